@@ -28,7 +28,7 @@ WORDS_PER_NODE_STEP = 7          # u_j, u_{j-1}, u_{j+1}, m, damping, Re F, Im F
 # a launch of k steps must read u_j, u_{j-1}, m, the damping factor and F
 # (2 words) and write u_{j+k}, u_{j+k-1}: 8 words per node, whatever k
 WORDS_PER_NODE_LAUNCH = 8
-RES_MAX_STEPS = 1024          # steps of one resident-tile launch (kernel 5)
+RES_MAX_STEPS = 4096          # steps of one resident-tile launch (kernel 5)
 # published MI355X vector peaks (TFLOP/s); the FP32 figure needs packed FP32
 # instructions, which this build does not emit (non-packed FP32 issues at the
 # FP64 rate)

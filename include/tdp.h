@@ -125,9 +125,9 @@ typedef struct {
  * alpha = (omega_c dt)^2 / (4 sin^2(omega_c dt / 2)),
  * beta = omega_c dt / sin(omega_c dt), lam_bar = upper bound on lambda_max(A),
  * lam_im = upper bound on lambda_max(Im H) with the cell damping (else 0).
- * res_aborts: resident-tile launches (tuning kernel 5) that ended early
- * because not every tile was resident; each such application was redone
- * with the blocked sweep, and the op's tuning went back to auto. */
+ * res_aborts: applications whose resident-tile launch (tuning kernel 5, or
+ * the automatic choice) ended early because not every tile was resident; each
+ * was redone (see tdp_tuning.kernel). */
 typedef struct {
     double omega_c, dt, alpha, beta, lam_bar;
     int n_P;
@@ -267,7 +267,10 @@ int tdp_gmres_solve(const tdp_op *op, const tdp_gmres_cfg *cfg, const void *F, v
 int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
 
 /* Tuning of the recurrence sweep (no effect on results beyond rounding).
- *  kernel       0 auto (kernel, depth and tile chosen by the library: the
+ *  kernel       0 auto (kernel, depth and tile chosen by the library: in 2-D
+ *               with node damping and no corner mass entries the resident
+ *               tiles (kernel 5) where the grid's tiles fit the device, at the
+ *               exchange depth of least cost, else the
  *               blocked 2-D sweep on tile 5 (FP64) or 8 (FP32) at depth 8, with
  *               the cell damping on tile 7 (FP64) or 4 (FP32); in 3-D the
  *               two-step streamed sweep for tables without corner entries
@@ -280,15 +283,22 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               variant), 4 streamed along axis 0 with two steps per launch
  *               (3-D, Table 1 variant), 5 resident tiles (2-D, node
  *               damping, tables without corner mass entries: each tile,
- *               88x64 in FP64 and 112x64 in FP32, stays on one compute unit
- *               for up to 1024 steps per launch and swaps k-wide halo bands
- *               with its neighbours through global memory every k steps; the
- *               tiles must fit the compute units and all be resident at
- *               once: when other work holds compute units a wait gives up,
- *               the application is redone with the blocked sweep and the
- *               op's tuning goes back to auto (tdp_op_info.res_aborts);
- *               where kernel 5 does not apply it falls back to the auto
- *               choice); inapplicable choices fall back to 1
+ *               48x64 in FP64 and 64x64 in FP32, two to a compute unit, stays
+ *               on chip for up to 4096 steps per launch and swaps k-wide halo
+ *               bands with its neighbours through global memory every k steps;
+ *               the tiles must all be resident at once, so the resident
+ *               launches of a process on one device are ordered one behind the
+ *               other, whatever their streams.  Where work of another process
+ *               holds compute units a wait gives up: with kernel = 5 and in
+ *               tdp_gmres_solve the application is redone with the blocked
+ *               sweep and the op's tuning goes back to auto; in a
+ *               tdp_precond_apply call under kernel 0, which stays
+ *               asynchronous, it is redone behind the run on the stream; either
+ *               way it is counted in tdp_op_info.res_aborts and the op's
+ *               automatic choice leaves this kernel out from then on, until
+ *               tdp_op_set_tuning.  Where kernel 5 does not apply it falls back
+ *               to the auto choice; a stream under capture takes the blocked
+ *               sweep); inapplicable choices fall back to 1
  *  tb_depth     kernel 2: steps per launch, 1..16 (0 auto);
  *               kernel 5: steps between halo exchanges, 2, 4, 6 or 8 (0: 4);
  *               kernel 3: planes per chunk (0 auto: 32, halved down
@@ -321,11 +331,10 @@ typedef struct {
 int tdp_op_set_tuning(tdp_op *op, const tdp_tuning *t);
 
 /* Test hook of the resident sweep's recovery path (tuning kernel 5): with
- * on = 1, each resident launch of this op waits for a flag value that no
- * tile writes, gives up after 16 polls and ends early, as it does when its
- * tiles are not all resident; the application is then redone with the
- * blocked sweep and counted in tdp_op_info.res_aborts.  on = 0 restores the
- * normal waits.  Returns TDP_OK or TDP_EINVAL. */
+ * on = 1, no poll of this op's resident launches succeeds: each gives up
+ * after 16 polls and ends early, as it does when its tiles are not all
+ * resident; the application is then redone and counted in
+ * tdp_op_info.res_aborts.  on = 0 restores the normal waits.  Returns TDP_OK or TDP_EINVAL. */
 int tdp_op_force_resident_abort(tdp_op *op, int on);
 
 /* Autotuner: times each sweep variant applicable to this op (one step per

@@ -3,6 +3,7 @@
 // (Sec. 2.4) and the m-gradient, behind the C ABI of include/tdp.h.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <complex>
@@ -10,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -119,8 +121,8 @@ static int free_op(tdp_op *op)
                     op->u3, op->u4, op->u5, op->rc, op->Fst, op->scratch, op->V, op->wv, op->tv, op->rv,
                     op->xv, op->red, op->dcoef};
     for (void *b : bufs) (void)hipFree(b);
-    (void)hipFree(op->res_shadow);
-    (void)hipFree(op->res_flags);
+    (void)hipFree(op->res_slots);
+    (void)hipFree(op->res_abort);
     for (auto &kv : op->dtables) (void)hipFree(kv.second);
     if (op->res_host) (void)hipHostFree(op->res_host);
     if (op->hres) (void)hipHostFree(op->hres);
@@ -409,6 +411,7 @@ extern "C" int tdp_op_set_tuning(tdp_op *op, const tdp_tuning *t)
             TDP_FAIL(TDP_EINVAL, "tiles 2, 8, 12 and 13 are FP32 only");
     }
     op->tune = *t;
+    op->res_off = false;
     return TDP_OK;
 }
 
@@ -540,28 +543,58 @@ static int ensure_complex_fields(tdp_op *op)
 
 // Which sweep kernel, depth and tile the loop uses: 1 one step per launch, 2
 // the blocked 2-D kernel (k steps per launch), 3 / 4 the streamed 3-D kernels
-// (depth = planes per chunk).  kernel 0 chooses all three: the blocked 2-D
-// sweep on the 32 x 64 tile (FP64) or the 128 x 64 tile (FP32) at depth 8,
-// the streamed 3-D sweep on 8 x 64 columns, with the chunk below.
-// Kernel 5, the resident-tile 2-D sweep (exchange depth = depth), applies to
-// Table 1 fields with node damping and tables without corner mass terms, on grids whose tiles fit the compute units (one workgroup each);
-// elsewhere, and for the allocation-free entry point (resident = false), the
-// plan falls back to the blocked sweep.
-static bool res_applies(const tdp_op *op, int k)
+// (depth = planes per chunk), 5 the resident-tile 2-D sweep (depth = steps
+// between exchanges).  kernel 0 chooses all three: in 2-D the resident sweep
+// where it applies, else the blocked one on the 32 x 64 tile (FP64) or the
+// 128 x 64 tile (FP32) at depth 8; in 3-D the two-step streamed sweep, or
+// the one-step one on 8 x 64 columns with the chunk below.
+// Kernel 5 applies to node damping and tables without corner mass terms, on
+// grids whose tiles are resident all at once; elsewhere, and with resident =
+// false (the allocation-free entry point, a stream under capture), the plan
+// falls back to the blocked sweep.
+static bool res_applies(const tdp_op *op, int k, int parts)
 {
-    const int nt = res_tiles(op->n[0], op->n[1], k, op->prec == TDP_F64, nullptr, nullptr);
-    return op->ndim == 2 && op->dform == TDP_DAMP_NODE && op->mc <= 2 && nt > 0 && nt <= op->ncu;
+    if (op->ndim != 2 || op->dform != TDP_DAMP_NODE || op->mc > 2) return false;
+    const bool f64 = op->prec == TDP_F64;
+    const int64_t nt = res_tiles(op->n[0], op->n[1], k, f64, nullptr, nullptr);
+    if (nt <= 0) return false;
+    return nt == 1 || nt * parts <= (int64_t)op->ncu * res_workgroups_per_cu(k, op->sc, f64);
+}
+
+// The automatic choice's exchange depth, 0 where the resident sweep does not
+// apply.  Model, measured per block of k steps (us): 2.5 for the exchange and
+// 0.6 a step with one workgroup per compute unit; 3 and 0.85 with two, which
+// share its vector units (256^2 FP64: 1.16 us a step at depth 4, 1.01 at depth
+// 8; 1024^2, 494 workgroups: 1.55 at depth 4, the deepest that fits).  The
+// blocked sweep takes 1.05 us a step on the smallest grids (a launch per 8
+// steps) and 3.0 at 1024^2, so the resident one is chosen wherever it fits.
+static int res_auto_depth(const tdp_op *op, int variant)
+{
+    const bool f64 = op->prec == TDP_F64;
+    int best = 0;
+    double best_us = 0.0;
+    for (int k = 8; k >= 2; k -= 2) {
+        if (!res_applies(op, k, 1)) continue;
+        const int parts = variant && res_applies(op, k, 2) ? 2 : 1;
+        const int nt = res_tiles(op->n[0], op->n[1], k, f64, nullptr, nullptr);
+        double us = nt * parts <= op->ncu ? 2.5 / k + 0.6 : 3.0 / k + 0.85;
+        if (variant) us *= 3 - parts;
+        if (!best || us < best_us) {
+            best = k;
+            best_us = us;
+        }
+    }
+    return best;
 }
 
 static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, int *tile,
                        bool resident = true)
 {
     int kern = op->tune.kernel, k = op->tune.tb_depth, t = op->tune.tile;
-    (void)variant;    // Definition 4 runs the same kernels as two real passes
     const bool f64 = op->prec == TDP_F64;
     if (kern == 5) {
         if (k == 0) k = 4;
-        if (resident && res_applies(op, k)) {
+        if (resident && res_applies(op, k, 1)) {
             *kernel = 5;
             *depth = k;
             *tile = 0;
@@ -571,6 +604,13 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
     }
     if (kern == 0) {
         if (op->ndim == 2) {
+            const int kr = resident && !op->res_off ? res_auto_depth(op, variant) : 0;
+            if (kr) {
+                *kernel = 5;
+                *depth = kr;
+                *tile = 0;
+                return;
+            }
             kern = 2;
             k = 8;
             t = f64 ? 5 : 8;
@@ -738,81 +778,157 @@ static int issue_steps_abd2(tdp_op *op, const LoopBufs &lb, int T, double rho, i
     return TDP_OK;
 }
 
-// Resident-tile loop (kernel 5): launches of up to TDP_RES_MAXSTEPS steps,
-// each preceded by a fill of the tile flags and the abort word, ping-ponging
-// between the field pairs (u0, u1) and (v0, v1).
-static int issue_steps_res(tdp_op *op, const LoopBufs &lb, int T, double rho, int k,
-                           const void *Fin, int tabv, double *out_final, double *out_snap)
+// Resident launches of the process on one device run one after the other: two
+// at once, on different streams, could each hold compute units that the
+// other's tiles wait for.  Each waits on the event of the last one.
+namespace {
+struct ResGate {
+    std::mutex mu;
+    hipEvent_t ev = nullptr;
+    uint64_t last = 0;             // op of the last launch (0: none yet)
+};
+ResGate g_res_gate[64];
+std::atomic<uint64_t> g_res_ids{0};
+}  // namespace
+
+// Resident-tile loop (kernel 5): launches of up to TDP_RES_MAXSTEPS steps over
+// every tile of `parts` real fields (2: both parts of Definition 4, in one
+// launch when the tiles fit), ping-ponging between the field pairs (u0, u1)
+// and (v0, v1) when there are several.
+static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, int variant,
+                           void *U, bool recover)
 {
     hipStream_t s = op->stream;
-    const int64_t Ns = (int64_t)T * op->nP, jsnap = out_snap ? Ns - snap_lag(op->nP) : -1;
-    auto it = op->dtables.find(std::make_tuple(T, rho, tabv));
-    if (it == op->dtables.end()) TDP_FAIL(TDP_EINVAL, "resident sweep: forcing table not staged");
-    ResArgs a;
+    const bool f64 = op->prec == TDP_F64;
+    const int64_t Ns = (int64_t)T * op->nP;
+    const int64_t jsnap = variant ? -1 : Ns - snap_lag(op->nP);
+    double *Ud = (double *)U;
+    ResArgs a{};
     a.ny = op->n[0];
     a.nx = op->n[1];
     a.sc = op->sc;
     a.k = k;
-    const bool f64 = op->prec == TDP_F64;
     const int nt = res_tiles(a.ny, a.nx, k, f64, &a.tiles_x, &a.tiles_y);
-    if (nt <= 0 || nt > op->res_ntiles) TDP_FAIL(TDP_EINVAL, "resident sweep: tile grid not set up");
     a.m = f64 ? (const void *)op->m : (const void *)op->m32;
     a.dn = f64 ? (const void *)op->dn : (const void *)op->dn32;
-    a.F = Fin;
-    a.shadow = op->res_shadow;
-    a.flags = op->res_flags;
-    a.poll_limit = op->res_force_abort ? 16 : (1 << 20);
-    a.wait_bias = op->res_force_abort ? (1 << 30) : 0;
-    const size_t fb = (f64 ? sizeof(double) : sizeof(float)) * op->N;
-    const size_t flag_bytes = sizeof(int) * ((size_t)nt * TDP_RES_FLAG_STRIDE + TDP_RES_FLAG_STRIDE);
-    void *cur = lb.u0, *prev = lb.u1, *ncur = lb.v0, *nprev = lb.v1;
-    TDP_CHECK_HIP(launch_fill_zero(cur, fb, s));
-    TDP_CHECK_HIP(launch_fill_zero(prev, fb, s));
-    for (int64_t j0 = 0; j0 < Ns; j0 += TDP_RES_MAXSTEPS) {
-        const int n = (int)std::min<int64_t>(TDP_RES_MAXSTEPS, Ns - j0);
-        a.nsteps = n;
-        a.u_in = cur;
-        a.up_in = prev;
-        a.u_out = ncur;
-        a.up_out = nprev;
-        a.tab = it->second + 2 * j0;
-        a.out_step[0] = (jsnap > j0 && jsnap <= j0 + n) ? (int)(jsnap - j0) : 0;
-        a.out[0] = out_snap;
-        a.out_step[1] = (Ns > j0 && Ns <= j0 + n) ? (int)(Ns - j0) : 0;
-        a.out[1] = out_final;
-        TDP_CHECK_HIP(launch_fill_zero(op->res_flags, flag_bytes, s));
-        if (f64)
-            TDP_CHECK_HIP(launch_sweep2d_res_f64(a, op->st_step, s));
-        else
-            TDP_CHECK_HIP(launch_sweep2d_res_f32(a, op->st_step32, s));
-        std::swap(cur, ncur);
-        std::swap(prev, nprev);
+    a.F = F;
+    a.slots = op->res_slots;
+    a.abort_word = op->res_abort;
+    a.poll_limit = op->res_force_abort ? 16 : (1 << 21);
+    a.wait_bias = op->res_force_abort ? 1 : 0;
+    const bool single = nt == 1;           // no exchange, nothing to wait for
+    // passes: Table 1's field; Definition 4's two parts together or in turn
+    const int together = variant && Ns <= TDP_RES_MAXSTEPS && res_applies(op, k, 2) ? 2 : 1;
+    ResGate &gate = g_res_gate[op->device & 63];
+    std::unique_lock<std::mutex> lock(gate.mu, std::defer_lock);
+    if (!single) {
+        lock.lock();
+        if (!gate.ev) TDP_CHECK_HIP(hipEventCreateWithFlags(&gate.ev, hipEventDisableTiming));
+        if (gate.last && gate.last != op->res_id) TDP_CHECK_HIP(hipStreamWaitEvent(s, gate.ev, 0));
+    }
+    bool first = true;
+    for (int p0 = 0; p0 < (variant ? 2 : 1); p0 += together) {
+        const double *tab[2] = {nullptr, nullptr};
+        a.parts = together;
+        for (int q = 0; q < together; ++q) {
+            auto it = op->dtables.find(std::make_tuple(T, rho, p0 + q ? 2 : 0));
+            if (it == op->dtables.end()) TDP_FAIL(TDP_EINVAL, "resident sweep: forcing table not staged");
+            tab[q] = it->second;
+            a.out[q][0] = variant ? nullptr : Ud + 1;
+            a.out[q][1] = Ud + p0 + q;
+        }
+        void *cur = op->u0, *prev = op->u1, *ncur = op->v0, *nprev = op->v1;
+        for (int64_t j0 = 0; j0 < Ns; j0 += TDP_RES_MAXSTEPS) {
+            const int n = (int)std::min<int64_t>(TDP_RES_MAXSTEPS, Ns - j0);
+            const bool last = j0 + n == Ns;
+            a.nsteps = n;
+            a.u_in = j0 ? cur : nullptr;
+            a.up_in = j0 ? prev : nullptr;
+            a.u_out = last ? nullptr : ncur;
+            a.up_out = last ? nullptr : nprev;
+            for (int q = 0; q < together; ++q) a.tab[q] = tab[q] + 2 * j0;
+            a.out_step[0] = (jsnap > j0 && jsnap <= j0 + n) ? (int)(jsnap - j0) : 0;
+            a.out_step[1] = last ? n : 0;
+            if (!single)
+                TDP_CHECK_HIP(launch_res_init(op->res_slots, res_slot_bytes(f64, k) * nt * together,
+                                              op->res_abort, first, f64, s));
+            first = false;
+            if (f64)
+                TDP_CHECK_HIP(launch_sweep2d_res_f64(a, op->st_step, s));
+            else
+                TDP_CHECK_HIP(launch_sweep2d_res_f32(a, op->st_step32, s));
+            std::swap(cur, ncur);
+            std::swap(prev, nprev);
+        }
+    }
+    if (!single) {
+        TDP_CHECK_HIP(hipEventRecord(gate.ev, s));
+        gate.last = op->res_id;
+    }
+    if (!single && recover) {
+        ResRecover r{};
+        r.ny = a.ny;
+        r.nx = a.nx;
+        r.parts = variant ? 2 : 1;
+        r.nsteps = Ns;
+        r.out_step[0] = jsnap;
+        r.out_step[1] = Ns;
+        r.u0 = op->u0;
+        r.u1 = op->u1;
+        r.m = a.m;
+        r.dn = a.dn;
+        r.F = F;
+        for (int q = 0; q < r.parts; ++q) {
+            r.tab[q] = op->dtables.at(std::make_tuple(T, rho, q ? 2 : 0));
+            r.out[q][0] = variant ? nullptr : Ud + 1;
+            r.out[q][1] = Ud + q;
+        }
+        r.abort_word = op->res_abort;
+        r.host_word = op->res_host + 1;
+        TDP_CHECK_HIP(launch_res_recover(r, op->st_step, op->st_step32, f64, s));
+    }
+    if (variant == 0 && op->nP % 4 != 0) {
+        const double phi = 2.0 * M_PI * (double)snap_lag(op->nP) / op->nP;
+        TDP_CHECK_HIP(launch_phase_extract(U, op->N, std::cos(phi), std::sin(phi), s));
     }
     return TDP_OK;
 }
 
-// Buffers of the resident sweep, allocated before any capture: exchange
-// buffer (two parities of every tile's two-level band), tile flags with the abort word, its pinned mirror, and device
-// copies of the forcing tables the loop reads.
-static int ensure_res(tdp_op *op, int T, double rho, int variant)
+// Buffers of the resident sweep: exchange slots of every tile, the abort word,
+// its pinned mirror, device copies of the forcing tables the loop reads, and
+// the field pairs that hand over between launches.
+static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
 {
-    if (!op->res_shadow) {
-        const size_t n = 2 * (size_t)op->ncu * std::max(res_band_bytes(true), res_band_bytes(false));
-        if (hipMalloc(&op->res_shadow, n) != hipSuccess)
-            TDP_FAIL(TDP_ENOMEM, "device allocation of the exchange buffer failed");
+    const bool f64 = op->prec == TDP_F64;
+    const int nt = res_tiles(op->n[0], op->n[1], k, f64, nullptr, nullptr);
+    if (!op->res_abort &&
+        (hipMalloc(&op->res_abort, sizeof(int)) != hipSuccess ||
+         hipHostMalloc(&op->res_host, 2 * sizeof(int)) != hipSuccess))
+        TDP_FAIL(TDP_ENOMEM, "allocation of the abort word failed");
+    if (!op->res_id) {
+        TDP_CHECK_HIP(hipMemset(op->res_abort, 0, sizeof(int)));
+        op->res_host[0] = op->res_host[1] = 0;
+        op->res_id = ++g_res_ids;
     }
-    if (!op->res_flags) {
-        const size_t n = (size_t)op->ncu * TDP_RES_FLAG_STRIDE + TDP_RES_FLAG_STRIDE;
-        if (hipMalloc(&op->res_flags, sizeof(int) * n) != hipSuccess ||
-            hipHostMalloc(&op->res_host, sizeof(int)) != hipSuccess)
-            TDP_FAIL(TDP_ENOMEM, "allocation of the tile flags failed");
-        op->res_ntiles = op->ncu;
+    if (nt > 1) {
+        const int parts = variant && res_applies(op, k, 2) ? 2 : 1;
+        const size_t n = res_slot_bytes(f64, k) * (size_t)nt * parts;
+        if (n > op->res_slots_bytes) {
+            TDP_CHECK_HIP(hipStreamSynchronize(op->stream));
+            (void)hipFree(op->res_slots);
+            op->res_slots = nullptr;
+            op->res_slots_bytes = 0;
+            if (hipMalloc(&op->res_slots, n) != hipSuccess)
+                TDP_FAIL(TDP_ENOMEM, "device allocation of the exchange slots failed");
+            op->res_slots_bytes = n;
+        }
     }
     const int tabvs[2] = {0, 2};
     for (int q = 0; q < (variant ? 2 : 1); ++q) {
         const auto key = std::make_tuple(T, rho, tabvs[q]);
         if (op->dtables.count(key)) continue;
-        const std::vector<double> &h = forcing_table(op, T, rho, tabvs[q]);
+        std::vector<double> h = forcing_table(op, T, rho, tabvs[q]);
+        h.resize(h.size() + 2 * 64);     // the kernel reads up to 64 steps ahead
         double *d = nullptr;
         if (hipMalloc(&d, sizeof(double) * h.size()) != hipSuccess)
             TDP_FAIL(TDP_ENOMEM, "device allocation of a forcing table failed");
@@ -822,18 +938,17 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant)
         }
         op->dtables.emplace(key, d);
     }
-    return TDP_OK;
+    return (int64_t)T * op->nP > TDP_RES_MAXSTEPS ? ensure_tb_fields(op) : TDP_OK;
 }
 
 // After a resident loop: the abort word is raised when a tile waited in vain
 // for a neighbour, which happens when not every tile was resident at once
-// (other work holding compute units).  Returns 1 then, else TDP_OK or a HIP
-// error.
-static int res_check(tdp_op *op, int ntiles)
+// (another process holding compute units).  Returns 1 then, else TDP_OK or a
+// HIP error.
+static int res_check(tdp_op *op)
 {
     hipStream_t s = op->stream;
-    TDP_CHECK_HIP(hipMemcpyAsync(op->res_host, op->res_flags + (size_t)ntiles * TDP_RES_FLAG_STRIDE,
-                                 sizeof(int), hipMemcpyDeviceToHost, s));
+    TDP_CHECK_HIP(hipMemcpyAsync(op->res_host, op->res_abort, sizeof(int), hipMemcpyDeviceToHost, s));
     TDP_CHECK_HIP(hipStreamSynchronize(s));
     return *op->res_host ? 1 : TDP_OK;
 }
@@ -959,10 +1074,9 @@ static int issue_steps_loop(tdp_op *op, const LoopBufs &lb, int T, double rho, i
                             const void *Fin, void *U)
 {
     int kern, depth, tile;
-    sweep_plan(op, variant, &kern, &depth, &tile, !lb.table_free);
+    sweep_plan(op, variant, &kern, &depth, &tile, false);
     double *Ud = (double *)U;
     auto real_pass = [&](int tabv, double *fin, double *snap) -> int {
-        if (kern == 5) return issue_steps_res(op, lb, T, rho, depth, Fin, tabv, fin, snap);
         if (kern == 2) return issue_steps_tb(op, lb, T, rho, depth, tile, Fin, tabv, fin, snap);
         if (kern == 4) return issue_steps_3d2(op, lb, T, rho, depth, tile, Fin, tabv, fin, snap);
         return issue_steps_real1(op, lb, T, rho, kern, depth, tile, Fin, tabv, fin, snap);
@@ -1028,16 +1142,17 @@ static int issue_steps(tdp_op *op, const LoopBufs &lb, int T, double rho, int va
     return TDP_OK;
 }
 
-static int res_finish(tdp_op *op, int ntiles, int T, double rho, int variant, const void *F,
-                      void *U, bool direct, int *pending);
+static int res_finish(tdp_op *op, int T, double rho, int variant, const void *F, void *U,
+                      bool direct, int *pending);
 
 // direct: F and U are buffers owned by the op (GMRES work vectors), so the
 // loop may be captured on them; otherwise a captured loop works on the
 // staging buffers, with copies of F in and U out around the replay.
+// The resident sweep is issued on F and U themselves, without a graph.
 // pending (GMRES): when the resident sweep ran, its abort word is copied to
-// op->res_host without waiting, and *pending receives its tile count (else
-// 0); the caller reads op->res_host at its next synchronisation and, if
-// the word is raised, calls res_redo for this application.
+// op->res_host without waiting, and *pending is 1 (else 0); the caller reads
+// op->res_host at its next synchronisation and, if the word is raised,
+// calls res_redo for this application.
 static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *F, void *U,
                         bool direct = false, int *pending = nullptr)
 {
@@ -1052,20 +1167,36 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
     if (Ns > TDP_MAX_STEPS)
         TDP_FAIL(TDP_EINVAL, "N_s = periods_T n_P = %lld exceeds 2^24", (long long)Ns);
     if (variant) TDP_CHECK(ensure_complex_fields(op));
+    // a recovery behind an earlier resident run redid its application: other
+    // work keeps the tiles from being resident together, so no more of them
+    if (op->res_host && *(volatile int *)(op->res_host + 1)) {
+        op->res_host[1] = 0;
+        ++op->res_aborts;
+        op->res_off = true;
+    }
+    // a stream that is being captured by the caller takes the blocked sweep
+    // (the resident launches are ordered against each other by events that a
+    // capture cannot hold)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (op->ndim == 2 && !op->own_stream) TDP_CHECK_HIP(hipStreamIsCapturing(op->stream, &cap));
+    const bool resident = cap == hipStreamCaptureStatusNone;
     int64_t launches;
-    int res_nt = 0;      // tiles of the resident sweep, when it runs
     {   // allocate before any stream capture: no allocation may happen inside it
         int kern, depth, tile;
-        sweep_plan(op, variant, &kern, &depth, &tile);
-        if (kern == 2 || kern == 4 || kern == 5) TDP_CHECK(ensure_tb_fields(op));
-        if (kern == 4) sweep3d_stream2_prepare(op->prec == TDP_F64, tile);
+        sweep_plan(op, variant, &kern, &depth, &tile, resident);
         if (kern == 5) {
-            TDP_CHECK(ensure_res(op, T, rho, variant));
-            res_nt = res_tiles(op->n[0], op->n[1], depth, op->prec == TDP_F64, nullptr, nullptr);
+            TDP_CHECK(ensure_res(op, T, rho, variant, depth));
+            // under kernel = 5 and in GMRES the host looks at the abort word;
+            // the automatic choice leaves the call asynchronous and puts the
+            // recovery behind the run on the stream
+            const bool recover = !pending && op->tune.kernel != 5;
+            TDP_CHECK(issue_steps_res(op, T, rho, depth, F, variant, U, recover));
+            return recover ? TDP_OK : res_finish(op, T, rho, variant, F, U, direct, pending);
         }
+        if (kern == 2 || kern == 4) TDP_CHECK(ensure_tb_fields(op));
+        if (kern == 4) sweep3d_stream2_prepare(op->prec == TDP_F64, tile);
         launches = kern == 2 ? (Ns + depth - 1) / depth
                  : kern == 4 ? (Ns + 1) / 2
-                 : kern == 5 ? 2 * ((Ns + TDP_RES_MAXSTEPS - 1) / TDP_RES_MAXSTEPS)
                              : Ns;
         // two real passes (one launch for both with the blocked I_abd kernel)
         if (variant == 1 && kern != 1 && !(op->dform == TDP_DAMP_CELL && kern == 2)) launches *= 2;
@@ -1080,8 +1211,7 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
             TDP_CHECK_HIP(launch_cvt_c128_to_c64(F, op->Fst, op->N, s));
             Fin = op->Fst;
         }
-        TDP_CHECK(issue_steps(op, lb, T, rho, variant, Fin, U));
-        return res_nt ? res_finish(op, res_nt, T, rho, variant, F, U, direct, pending) : TDP_OK;
+        return issue_steps(op, lb, T, rho, variant, Fin, U);
     }
     // captured loop: on F and U themselves (direct), else reading op->Fstage
     // (F64) / op->Fst (F32) and writing op->Ustage
@@ -1126,7 +1256,7 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
     }
     if (direct) {
         TDP_CHECK_HIP(hipGraphLaunch(it->second, s));
-        return res_nt ? res_finish(op, res_nt, T, rho, variant, F, U, direct, pending) : TDP_OK;
+        return TDP_OK;
     }
     if (op->prec == TDP_F64)
         TDP_CHECK_HIP(hipMemcpyAsync(op->Fstage, F, 16 * op->N, hipMemcpyDeviceToDevice, s));
@@ -1134,7 +1264,7 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
         TDP_CHECK_HIP(launch_cvt_c128_to_c64(F, op->Fst, op->N, s));
     TDP_CHECK_HIP(hipGraphLaunch(it->second, s));
     TDP_CHECK_HIP(hipMemcpyAsync(U, op->Ustage, 16 * op->N, hipMemcpyDeviceToDevice, s));
-    return res_nt ? res_finish(op, res_nt, T, rho, variant, F, U, direct, pending) : TDP_OK;
+    return TDP_OK;
 }
 
 // A resident loop that ended early is redone with the blocked sweep, and the
@@ -1143,22 +1273,23 @@ static int res_redo(tdp_op *op, int T, double rho, int variant, const void *F, v
                     bool direct)
 {
     ++op->res_aborts;
+    op->res_off = true;
     op->tune.kernel = 0;
     op->tune.tb_depth = 0;
     op->tune.tile = 0;
     return precond_impl(op, T, rho, variant, F, U, direct);
 }
 
-static int res_finish(tdp_op *op, int ntiles, int T, double rho, int variant, const void *F,
-                      void *U, bool direct, int *pending)
+static int res_finish(tdp_op *op, int T, double rho, int variant, const void *F, void *U,
+                      bool direct, int *pending)
 {
     if (pending) {          // the caller reads the word at its next synchronisation
-        TDP_CHECK_HIP(hipMemcpyAsync(op->res_host, op->res_flags + (size_t)ntiles * TDP_RES_FLAG_STRIDE,
-                                     sizeof(int), hipMemcpyDeviceToHost, op->stream));
-        *pending = ntiles;
+        TDP_CHECK_HIP(hipMemcpyAsync(op->res_host, op->res_abort, sizeof(int),
+                                     hipMemcpyDeviceToHost, op->stream));
+        *pending = 1;
         return TDP_OK;
     }
-    const int rc = res_check(op, ntiles);
+    const int rc = res_check(op);
     if (rc != 1) return rc;
     return res_redo(op, T, rho, variant, F, U, direct);
 }
@@ -1232,7 +1363,7 @@ extern "C" int tdp_op_autotune(tdp_op *op, int periods_T, double rho, int varian
         }
     }
     for (int k : {2, 4, 6, 8})
-        if (res_applies(op, k)) cand.push_back({5, k, 1, 0});
+        if (res_applies(op, k, 1)) cand.push_back({5, k, 1, 0});
     if (op->ndim == 2 && op->dform == TDP_DAMP_CELL && op->mc <= 2) {
         for (int tile = 4; tile <= 7; ++tile) {
             if (!abd_tile_ok(tile, op->prec == TDP_F64)) continue;

@@ -1,40 +1,69 @@
-// Resident-tile 2-D recurrence sweep: the Table 1 loop on the real field
+// Resident-tile 2-D recurrence sweep: the Table 1 loop on a real field
 // (integrator I_acd of Def. 2) for tables without corner mass terms, with
 // every tile held on chip for a whole run of steps.
 //
 // The blocked kernels of sweep_tb.hip reload their tile and refold its
 // coefficients for every k steps, and a launch of them is bound by that
 // prologue and by the scheduling of a few thousand workgroups.  Here one
-// workgroup per compute unit owns one tile for up to TDP_RES_MAXSTEPS steps:
+// workgroup owns one tile for up to TDP_RES_MAXSTEPS steps:
 // - at the start it loads the extended tile (exact region plus a k-wide halo)
-//   once, folds the cell slowness into per-node coefficients premultiplied
-//   by the damping factor d, and keeps d F in LDS;
+//   once and folds the cell slowness into per-node coefficients; F is kept in
+//   LDS;
 // - it then advances k steps at a time in registers, exactly as the blocked
 //   tile does (rows per lane, DPP x-neighbours, edge rows through LDS, one
 //   barrier per step);
-// - after each block of k steps it publishes the k-wide border band of its
-//   exact region (u_j and u_{j-1}) to its slot of a global exchange buffer
-//   and raises its flag; each wave then waits for the flags of the
-//   neighbours whose bands it reads (west and east, and the three tiles above
-//   or below for the waves holding top or bottom halo rows: the tile as a
-//   whole waits for all eight) and reads its halo from their bands.
-// A band is packed: the k top rows and the k bottom rows of the exact region
-// (full width), then the k left and the k right columns of the rows between
-// them, each a row-major block.  It is staged in LDS and copied out with whole-line
-// stores; a halo node is read from the band of the tile that owns it.
-// The exchange buffer and flags are accessed only with agent-scope relaxed
-// atomics, which the compiler emits with the coherent cache policy (sc1):
-// they bypass the per-XCD L2 state that is not kept coherent between XCDs.
-// A tile's band stores are complete (s_waitcnt) before its flag store is
-// issued, and its neighbours issue their band loads only after reading that
-// flag, so no L2 writeback or invalidate (the cost of a release/acquire
-// fence at agent scope) is needed.  Bands are double-buffered by block
-// parity: a tile rewrites a parity only after its neighbours have raised the
-// next block's flag, i.e. after they have read that parity.
-// Every tile must be resident at once.  A wait that exceeds its poll limit,
-// or sees another tile's abort, raises the abort word and the whole grid
-// leaves early; the host checks that word after the launch.
+// - after each block of k steps it publishes the border of its exact region
+//   (u_j and u_{j-1}) to its slot of a global exchange buffer and reads its
+//   halo from its neighbours' slots.
+//
+// Two workgroups share a compute unit (at most 80 KB of LDS and 256 VGPRs on 4
+// waves each), so that one computes while the other waits for its halo: a
+// block's exchange is a chain of memory round trips through the fabric, about
+// as long as four steps, and nothing inside one tile can hide it.  Measured at
+// 1024^2 in FP64 (494 tiles of 48 x 64, k = 4): 1.55 us a step, against 2.21
+// with one 88 x 64 tile per compute unit, flags and acknowledged bands, and 3.0
+// for the blocked sweep; in FP32 (441 tiles of 64 x 64, k = 8) 1.12 against 1.63
+// (112 x 64 tiles) and 1.93.  Of a 4-step block's 14.1 k cycles (mean over
+// tiles) 6.3 k are steps (5.4 k where a tile has the vector units to itself,
+// 8.1 k in the younger of two that run together), 1.6 k stage and publish,
+// 2.5-5 k wait for the neighbours' words, the rest is barriers, the landing
+// and the emptied slot.  Bound by the vector units while the two compute
+// together (a step issues 930 of its 1375 cycles) and by the round trip between.
+//
+// Exchange without flags.  A slot holds a reserved signalling-NaN pattern
+// until its tile publishes; a reader loads the halo values themselves and
+// loads again while any of them is that pattern.  The arithmetic never makes
+// it (results that are NaN are quiet), so a value that is not the pattern is
+// the published one.  This saves the two round trips of a flag protocol (the
+// band stores acknowledged before the flag store, the flag seen before the
+// band loads).  Slots are used in turn, three per tile:
+//   exchange e publishes in slot e mod 3, reads the neighbours' slots e mod
+//   3, and then, with every neighbour's exchange-e data in hand, so that all of
+//   them have read this tile's exchange e-1, returns slot (e-1) mod 3 to the
+//   pattern.  Those stores are complete (s_waitcnt, barrier) before exchange
+//   e+1 publishes, so a neighbour that polls for exchange e+2 in that slot,
+//   which it does only after it has read exchange e+1, finds the pattern or
+//   new values, never old ones.
+// Values travel whole: 64- or 32-bit agent-scope relaxed atomics, which the
+// compiler emits with the coherent cache policy (sc1): they bypass the
+// per-XCD L2 state that is not kept coherent between XCDs.
+//
+// Tile geometry: tile (ty, tx) extends over rows ty OY .. ty OY + EY - 1 and
+// columns tx OX .. tx OX + 63, OX = 64 - 2k, OY = EY - 2k; the k outermost
+// rows and columns are halo where a neighbour exists, while at the domain's
+// edge the exact region reaches it (nothing is lost to a halo there: a
+// Dirichlet wall needs none).  A grid of one tile needs no exchange at all.
+// A slot holds, per level, the k rows above and below the halo rows over all
+// 64 columns and the k columns beside the halo columns over all EY rows.
+//
+// Every tile must be resident at once: the host launches no more workgroups
+// than the device holds, and one such launch at a time.  A wait that exceeds
+// its poll limit, or sees another tile's abort, raises the abort word and the
+// whole grid leaves early; the host, or k_res_recover behind it on the
+// stream, then redoes the application.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "tdp_internal.h"
 #include "lanes.h"
@@ -43,13 +72,7 @@ namespace tdp {
 
 namespace {
 
-constexpr int kResW = 8;            // waves per workgroup (2 per SIMD)
-constexpr int kResR64 = 11;         // rows per lane, FP64: 88 x 64 extended tile
-constexpr int kResR32 = 14;         // rows per lane, FP32: 112 x 64 (one word per node value)
-constexpr int kResKMax = 8;
-
-// values per level of the largest band (depth 8) of a tile with EY rows
-constexpr int res_band_max(int EY) { return 2 * kResKMax * (64 - 2 * kResKMax) + 2 * (EY - 4 * kResKMax) * kResKMax; }
+constexpr int kResX = 64;           // columns of an extended tile (one wave)
 
 template <typename T>
 __device__ __forceinline__ void st_coh(T *p, T v)
@@ -62,10 +85,196 @@ __device__ __forceinline__ T ld_coh(const T *p)
     return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A zero the optimiser cannot see through.  Added once per block to the
-// tile's row origin, it keeps the per-row addresses and conditions of the
-// exchange and snapshot code inside the block loop: hoisted, the eleven rows'
-// worth of them would take the registers the tile needs.
+// The exchange moves field values as words: a comparison of floating-point
+// values cannot tell one NaN from another.
+template <typename T>
+struct Word;
+template <>
+struct Word<double> {
+    using type = unsigned long long;
+    static constexpr type empty = 0x7FF4A11FEE11C0DEull;      // quiet bit clear
+    static __device__ __forceinline__ type of(double v) { return (type)__double_as_longlong(v); }
+    static __device__ __forceinline__ double value(type w) { return __longlong_as_double((long long)w); }
+};
+template <>
+struct Word<float> {
+    using type = unsigned;
+    static constexpr type empty = 0x7FA1C0DEu;
+    static __device__ __forceinline__ type of(float v) { return __float_as_uint(v); }
+    static __device__ __forceinline__ float value(type w) { return __uint_as_float(w); }
+};
+
+// words per level of a tile's slot
+constexpr int res_band(int EY, int K) { return 2 * K * kResX + 2 * K * EY; }
+
+// Per-node coefficients of a wave's R rows and the update of one row.
+// FP64: the stencil weights without the damping factor d, which is applied
+// once per update,
+//   u_{j+1} = d (sum_q w_q u_j(q) + fa Re F + fb Im F - 2 u_{j-1}) + u_{j-1}:
+// the weight of the edge between rows i and i+1 serves both (R + 1 per lane)
+// and the corner weight is uniform, so a node holds 7 words with its two
+// levels instead of 8, which is what lets 12 rows fit 256 VGPRs.
+// FP32: the coefficients premultiplied by d, as in the blocked tile's second
+// form and in its order of operations (the results are the same, bit for
+// bit); registers are not short there.
+template <typename T, int SC, int R>
+struct Rows;
+
+template <int SC, int R>
+struct Rows<double, SC, R> {
+    double wc[R], ww[R], we[R], wy[R + 1], d[R];
+    double s2;
+    __device__ __forceinline__ void fold(const Stencil<double> &st, const double (&ca)[R + 1],
+                                         const double (&cb)[R + 1], const double (&dd)[R])
+    {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            wc[i] = st.c0 + st.m[0] * ((ca[i] + cb[i]) + (ca[i + 1] + cb[i + 1]));
+            ww[i] = st.s[1] + st.m[1] * (ca[i] + ca[i + 1]);
+            we[i] = st.s[1] + st.m[1] * (cb[i] + cb[i + 1]);
+            d[i] = dd[i];
+        }
+#pragma unroll
+        for (int i = 0; i <= R; ++i) wy[i] = st.s[1] + st.m[1] * (ca[i] + cb[i]);
+        s2 = st.s[2];
+    }
+    __device__ __forceinline__ double2 forcing(int, double2 f) const { return f; }
+    __device__ __forceinline__ double update(int i, double cc, double cw, double ce, double pc,
+                                             double xc, double corners, double2 f, double fas,
+                                             double fbs, double prev) const
+    {
+        double acc = wc[i] * cc;
+        acc += ww[i] * cw;
+        acc += we[i] * ce;
+        acc += wy[i] * pc;
+        acc += wy[i + 1] * xc;
+        if (SC > 2) acc += s2 * corners;
+        acc += fas * f.x;
+        acc += fbs * f.y;
+        acc += -2.0 * prev;
+        return d[i] * acc + prev;
+    }
+};
+
+template <int SC, int R>
+struct Rows<float, SC, R> {
+    float co[R][5], d[R];
+    float s2;
+    __device__ __forceinline__ void fold(const Stencil<float> &st, const float (&ca)[R + 1],
+                                         const float (&cb)[R + 1], const float (&dd)[R])
+    {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            fold_node<float, 2, 2, 5>(st, dd[i], ca[i], cb[i], ca[i + 1], cb[i + 1], co[i]);
+            d[i] = dd[i];
+        }
+        s2 = st.s[2];
+    }
+    __device__ __forceinline__ float2 forcing(int i, float2 f) const
+    {
+        f.x *= d[i];
+        f.y *= d[i];
+        return f;
+    }
+    __device__ __forceinline__ float update(int i, float cc, float cw, float ce, float pc, float xc,
+                                            float corners, float2 f, float fas, float fbs,
+                                            float prev) const
+    {
+        float acc = co[i][0] * cc;
+        acc += co[i][1] * cw;
+        acc += co[i][2] * ce;
+        acc += co[i][3] * pc;
+        acc += co[i][4] * xc;
+        if (SC > 2) acc += (d[i] * s2) * corners;
+        acc += fas * f.x;
+        acc += fbs * f.y;
+        return acc + (1.0f - 2.0f * d[i]) * prev;
+    }
+};
+
+// x-1, x, x+1 of one row, and the sum of the outer two (shared by the corner
+// terms of the rows above and below)
+template <typename T>
+struct Row3 {
+    T w, c, e, s;
+};
+template <typename T>
+__device__ __forceinline__ Row3<T> row_of(T c)
+{
+    Row3<T> r;
+    r.c = c;
+    r.w = lane_west(c);
+    r.e = lane_east(c);
+    r.s = r.w + r.e;
+    return r;
+}
+template <typename T>
+__device__ __forceinline__ Row3<T> row_at(const T *p)
+{
+    Row3<T> r;
+    r.w = p[-1];
+    r.c = p[0];
+    r.e = p[1];
+    r.s = r.w + r.e;
+    return r;
+}
+
+// One step of the wave's R rows: the halo rows south and north come from the
+// edge-row slots around cur[rs] and cur[rn]; the new first and last rows go to
+// nxt[wf] and nxt[wl].  b holds u_{j-1} on entry and u_{j+1} on exit.
+// With one or two waves per SIMD the step is bound by latency.  An update is
+// one chain of dependent operations, so two rows are updated at a time, and
+// the next two rows' F is read from LDS meanwhile.  The pairs go down from
+// the second to the first and then from the last to the third: the halo rows
+// are needed only after the first pair, and the new edge rows are in LDS
+// while the inner pairs are still to do, so that neither LDS latency stands
+// beside the barrier.
+template <typename T, int SC, int R>
+__device__ __forceinline__ void res_step(const T *__restrict__ cur, T *__restrict__ nxt, int rs,
+                                         int rn, int wf, int wl,
+                                         const typename V2t<T>::type *__restrict__ fl,
+                                         const Rows<T, SC, R> &co, const T (&a)[R], T (&b)[R],
+                                         T fas, T fbs)
+{
+    static_assert(R % 2 == 0 && R >= 8, "rows go in pairs");
+    constexpr int NP = R / 2;
+    auto f0 = fl[2 * kResX], f1 = fl[3 * kResX];
+    const Row3<T> south = row_at(cur + rs), north = row_at(cur + rn);
+    Row3<T> x = row_of(a[3]), y = row_of(a[4]);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        // pair i: rows 2i-1 (p), 2i (c), 2i+1 (x), 2i+2 (y)
+        const int i = q < 2 ? 1 - q : NP + 1 - q, n = q < 1 ? 0 : NP - q;
+        if (q == 2) {
+            x = row_of(a[R - 1]);
+            y = north;
+        }
+        const Row3<T> c = row_of(a[2 * i]);
+        const Row3<T> p = i > 0 ? row_of(a[2 * (i > 0 ? i : 1) - 1]) : south;
+        auto g0 = f0, g1 = f1;
+        if (q + 1 < NP) {                // pair n is next
+            g0 = fl[2 * n * kResX];
+            g1 = fl[(2 * n + 1) * kResX];
+        }
+        b[2 * i] = co.update(2 * i, c.c, c.w, c.e, p.c, x.c, p.s + x.s, f0, fas, fbs, b[2 * i]);
+        b[2 * i + 1] = co.update(2 * i + 1, x.c, x.w, x.e, c.c, y.c, c.s + y.s, f1, fas, fbs,
+                                 b[2 * i + 1]);
+        if (i == 0) nxt[wf] = b[0];
+        if (i == NP - 1) nxt[wl] = b[R - 1];
+        x = p;
+        y = c;
+        f0 = g0;
+        f1 = g1;
+        // keep the window a window: hoisting later rows' shifts would make
+        // every row's neighbours live at once
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// A zero the optimiser cannot see through.  Added to a wave's first row where
+// samples are written, and to the lane in the exchange, it keeps the
+// addresses and conditions of that code there: hoisted out of the block
+// loop, the rows' worth of them would take the registers the tile needs.
 __device__ __forceinline__ int opaque_zero()
 {
     int z;
@@ -73,344 +282,555 @@ __device__ __forceinline__ int opaque_zero()
     return z;
 }
 
-// One step of the wave's R rows (the blocked tile's second form with d F read
-// from LDS): rows r0-1 .. r0+R at x-1, x, x+1 are walked as a rolling window
-// of three rows; the halo rows south and north come from the edge-row slots
-// cur[rs - 1 .. rs + 1] and cur[rn - 1 .. rn + 1]; the new first and last
-// rows go to nxt[wf] and nxt[wl].  b holds u_{j-1} on entry and u_{j+1} on
-// exit.  The corner weight d s_2 is rebuilt from e = 1 - 2d as
-// s_2/2 - (s_2/2) e, one FMA instead of a register per node.
-template <typename T, int SC, int R>
-__device__ __forceinline__ void res_step(const T *__restrict__ cur, T *__restrict__ nxt, int rs,
-                                         int rn, int wf, int wl,
-                                         const typename V2t<T>::type *__restrict__ fl,
-                                         const T (&co)[R][5], const T (&e)[R], T s2h,
-                                         const T (&a)[R], T (&b)[R], T fas, T fbs)
-{
-    constexpr bool CORNER = SC > 2;
-    T pc = cur[rs];
-    T ps = cur[rs - 1] + cur[rs + 1];        // W + E of the row below
-    T cw = lane_west(a[0]), cc = a[0], ce = lane_east(a[0]);
-    T cs = cw + ce;
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-        T xw, xc, xe;
-        if (i + 1 < R) {
-            xc = a[i + 1];
-            xw = lane_west(xc);
-            xe = lane_east(xc);
-        } else {
-            xw = cur[rn - 1];
-            xc = cur[rn];
-            xe = cur[rn + 1];
-        }
-        const T xs = xw + xe;
-        const auto f = fl[i * 64];
-        T acc = co[i][0] * cc;
-        acc += co[i][1] * cw;
-        acc += co[i][2] * ce;
-        acc += co[i][3] * pc;
-        acc += co[i][4] * xc;
-        if (CORNER) acc += (s2h - s2h * e[i]) * (ps + xs);
-        acc += fas * f.x;
-        acc += fbs * f.y;
-        b[i] = acc + e[i] * b[i];
-        pc = cc;
-        ps = cs;
-        cw = xw;
-        cc = xc;
-        ce = xe;
-        cs = xs;
-        // keep the window a window: hoisting later rows' shifts would make
-        // every row's neighbours live at once
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    nxt[wf] = b[0];
-    nxt[wl] = b[R - 1];
-}
+// LDS of one tile: the packed edge-row slots (two copies), F, and the staging
+// of the exchange: the border columns being published, later each wave's
+// incoming halo columns.
+template <typename T, int R, int W, int K, bool MULTI>
+struct ResLds {
+    static constexpr int EY = R * W;
+    static constexpr int CB = (2 * W + 2) * (kResX + 2);
+    static constexpr int BAND = res_band(EY, K);
+    static constexpr int LAND = 4 * R * K;                     // words per wave
+    static constexpr int STAGE = MULTI ? 4 * K * EY : 1;       // = W * LAND
+};
 
-template <typename T, int SC, int R, int W>
-__global__ __launch_bounds__(64 * W) void k_sweep2d_res(ResArgs a, Stencil<T> st)
+template <typename T, int SC, int R, int W, int K, bool MULTI>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2)))
+void k_sweep2d_res(ResArgs a, Stencil<T> st)
 {
     using V2 = typename V2t<T>::type;
-    constexpr int EX = 64, EY = R * W;
-    constexpr int US = EX + 2;
-    constexpr int CB = (2 * W + 2) * US;          // packed edge-row slots of one copy
+    using Wd = Word<T>;
+    using word = typename Wd::type;
+    using L = ResLds<T, R, W, K, MULTI>;
+    constexpr int EX = kResX, EY = L::EY, US = EX + 2, CB = L::CB, BAND = L::BAND;
+    constexpr int OX = EX - 2 * K, OY = EY - 2 * K;
     __shared__ T xl[2 * CB];
-    __shared__ V2 fl_all[EY * EX];                // d F of the extended tile
-    __shared__ double fab[2 * TDP_RES_MAXSTEPS];  // forcing scalars of the launch
-    __shared__ T sband[2 * res_band_max(EY)];      // the band being published
+    __shared__ V2 fl_all[EY * EX];
+    __shared__ word stage[L::STAGE];
+    __shared__ double2 fab[64];
     __shared__ int s_abort;
 
-    const int ny = a.ny, nx = a.nx, k = a.k, nsteps = a.nsteps;
-    const int OX = EX - 2 * k, OY = EY - 2 * k;
-    const int tile = blockIdx.x;
+    const int ny = a.ny, nx = a.nx, nsteps = a.nsteps;
+    const int ntl = a.tiles_x * a.tiles_y;
+    const int part = (int)blockIdx.x >= ntl ? 1 : 0;
+    const int tile = blockIdx.x - part * ntl;
     const int ty = tile / a.tiles_x, tx = tile - ty * a.tiles_x;
-    const int gy0 = ty * OY - k, gx0 = tx * OX - k;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, lane_ = lane;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = wv * R;
-    const int gx = gx0 + lane;
-    const bool xin = (unsigned)gx < (unsigned)nx;
-    // the exact region of this tile (clipped to the domain)
-    const int ey0 = ty * OY, ey1 = min(ny, ey0 + OY);
-    const int ex0 = tx * OX, ex1 = min(nx, ex0 + OX);
-    const bool xexact = gx >= ex0 && gx < ex1;
-    // the band is defined on the unclipped tile: a border cut by
-    // the domain edge has no neighbour to publish to
-    const bool xband = xexact && (gx < ex0 + k || gx >= ex0 + OX - k);
-    const bool xhalo = lane < k || lane >= k + OX;
-    const int band = 2 * k * OX + 2 * (OY - 2 * k) * k;   // values per level
-    const int ntl = a.tiles_x * a.tiles_y;
-    // per lane: the owner tile column and local column of its x
-    const int txo = gx >= 0 ? gx / OX : -1, lxo = gx - txo * OX;
-    const int lx = gx - ex0;                               // local column in this tile
-    T *const shadow = (T *)a.shadow;
-    int *const flags = a.flags;
-    int *const abort_word = a.flags + a.tiles_x * a.tiles_y * TDP_RES_FLAG_STRIDE;
-
-    if (threadIdx.x == 0) s_abort = 0;
-    for (int t = threadIdx.x; t < 2 * nsteps; t += 64 * W) fab[t] = a.tab[t];
+    const int gy0 = ty * OY, gx = tx * OX + lane;
+    const bool xin = gx < nx;
+    // which sides of the tile have a neighbour (elsewhere: the domain's edge)
+    const bool nbW = MULTI && tx > 0, nbE = MULTI && tx + 1 < a.tiles_x;
+    const bool nbS = MULTI && ty > 0, nbN = MULTI && ty + 1 < a.tiles_y;
+    const bool xexact = xin && (!nbW || lane >= K) && (!nbE || lane < EX - K);
+    // forcing scalars, a ring of 64 steps in LDS refilled 32 at a time: read
+    // from memory as they are used, by vector or by scalar loads (whose wait
+    // is shared with the LDS reads'), they cost a round trip per step
+    const double *const tab = a.tab[part];
+    double *const out0 = a.out[part][0], *const out1 = a.out[part][1];
+    int *const abort_word = a.abort_word;
+    if (MULTI && threadIdx.x == 0) s_abort = 0;
+    if (threadIdx.x < 128) ((double *)fab)[threadIdx.x] = tab[threadIdx.x];
     for (int t = threadIdx.x; t < 2 * CB; t += 64 * W) xl[t] = T(0);
 
-    // the extended tile: cells, u_j, u_{j-1}, d, F; every load is issued
-    // before the first use
-    T co[R][5], e[R];        // centre, W, E, S, N times d; 1 - 2d
-    const T s2h = T(0.5) * st.s[2];
+    // the extended tile: cells, d, F and, for a run that continues another
+    // launch, u_j and u_{j-1} (else they start from zero); every load is
+    // issued before the first use
+    Rows<T, SC, R> co;
     T u0[R], u1[R];
     {
-        const T *m = (const T *)a.m;
-        const T *dn = (const T *)a.dn;
-        const V2 *F = (const V2 *)a.F;
+        const T *m = (const T *)a.m, *dn = (const T *)a.dn;
+        const double2 *F = (const double2 *)a.F;
         const T *u_in = (const T *)a.u_in, *up_in = (const T *)a.up_in;
         T ca[R + 1], cb[R + 1], d[R];
-        V2 f[R];
+        double2 f[R];
 #pragma unroll
         for (int i = 0; i <= R; ++i) {
             const int sy = gy0 + r0 + i;
-            const bool rok = (unsigned)sy <= (unsigned)ny;
             const T *mrow = m + (int64_t)sy * (nx + 1);
-            ca[i] = (rok && (unsigned)gx <= (unsigned)nx) ? mrow[gx] : T(0);
-            cb[i] = (rok && (unsigned)(gx + 1) <= (unsigned)nx) ? mrow[gx + 1] : T(0);
+            ca[i] = (sy <= ny && gx <= nx) ? mrow[gx] : T(0);
+            cb[i] = (sy <= ny && gx + 1 <= nx) ? mrow[gx + 1] : T(0);
         }
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int gy = gy0 + r0 + i;
-            const bool in = xin && (unsigned)gy < (unsigned)ny;
             const int64_t row = (int64_t)gy * nx;
             u0[i] = u1[i] = d[i] = T(0);
-            f[i].x = f[i].y = T(0);
-            if (in) {
-                u0[i] = (u_in + row)[gx];
-                u1[i] = (up_in + row)[gx];
+            f[i].x = f[i].y = 0.0;
+            if (xin && gy < ny) {
                 d[i] = (dn + row)[gx];
                 f[i] = (F + row)[gx];
+                if (u_in) {
+                    u0[i] = (u_in + row)[gx];
+                    u1[i] = (up_in + row)[gx];
+                }
             }
         }
+        co.fold(st, ca, cb, d);
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            fold_node<T, 2, 2, 5>(st, d[i], ca[i], cb[i], ca[i + 1], cb[i + 1], co[i]);
-            e[i] = T(1) - T(2) * d[i];
-            f[i].x *= d[i];
-            f[i].y *= d[i];
-            fl_all[(r0 + i) * 64 + lane] = f[i];
+            V2 v;
+            v.x = (T)f[i].x;
+            v.y = (T)f[i].y;
+            fl_all[(r0 + i) * EX + lane] = co.forcing(i, v);
         }
     }
     const int rs = 2 * wv * US + lane + 1, rn = (2 * wv + 3) * US + lane + 1;
     const int wf = (2 * wv + 1) * US + lane + 1, wl = (2 * wv + 2) * US + lane + 1;
     T *const c0 = xl, *const c1 = xl + CB;
-    const V2 *fl = fl_all + r0 * 64 + lane;
+    const V2 *fl = fl_all + r0 * EX + lane;
+
+    // the exchange: words of the halo columns this lane fetches (per level,
+    // side, row and column of the wave's rows), as offsets into the exchange
+    // slots of one parity.  A halo row's columns belong to a diagonal
+    // neighbour, whose rows are OY further on (south) or back (north)
+    constexpr int NQ = MULTI ? (L::LAND + 63) / 64 : 1;
+    int off[NQ];
+    word *const slots = (word *)a.slots;
+    const int64_t slot_words = (int64_t)2 * BAND;
+    const int64_t par_words = slot_words * gridDim.x;
+    word *const mine = slots + blockIdx.x * slot_words;
+    const int lo_row = nbS ? K : 0, hi_row = nbN ? EY - K : EY;   // rows that are not halo
+    if constexpr (MULTI) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int e = q * 64 + lane;
+            const int lev = e / (2 * R * K), side = e / (R * K) & 1;
+            const int i = e / K % R, c = e % K, r = r0 + i;
+            const bool south = r < lo_row, north = r >= hi_row;
+            const int nb = (side ? 1 : -1) + (south ? -a.tiles_x : (north ? a.tiles_x : 0));
+            const int ro = south ? r + OY : (north ? r - OY : r);
+            off[q] = e < L::LAND && (side ? nbE : nbW)
+                         ? nb * (int)slot_words + lev * BAND + 2 * K * EX + (side ? 0 : K * EY) +
+                               ro * K + c
+                         : INT32_MIN;
+        }
+    }
     __syncthreads();
     c0[wf] = u0[0];
     c0[wl] = u0[R - 1];
     __syncthreads();
 
-    int gyw = gy0 + r0;   // first global row of the wave (made opaque per block)
-    auto exact_node = [&](int i) {
-        const int gy = gyw + i;
-        return xexact && gy >= ey0 && gy < ey1;
-    };
-    auto snapshot = [&](int step, const T(&v)[R]) {   // step: 1-based within the launch
+    auto snapshot = [&](int step, const T(&v)[R]) __attribute__((always_inline)) {   // step: 1-based within the launch
         if (step == a.out_step[0] || step == a.out_step[1]) {
-            double *o = step == a.out_step[0] ? a.out[0] : a.out[1];
+            double *o = step == a.out_step[0] ? out0 : out1;
+            const int rb = r0 + opaque_zero();
+            const int re = min(hi_row, ny - gy0);
+            double *p = o + 2 * ((int64_t)(gy0 + rb) * nx + gx);
+            if (xexact) {
 #pragma unroll
-            for (int i = 0; i < R; ++i)
-                if (exact_node(i)) (o + 2 * (int64_t)(gyw + i) * nx)[2 * gx] = (double)v[i];
+                for (int i = 0; i < R; ++i) {
+                    if (rb + i >= lo_row && rb + i < re) *p = (double)v[i];
+                    p += 2 * (int64_t)nx;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
         }
     };
 
-    // A block ends at every sample step, so that the samples are written
-    // outside the unrolled steps; after a block of odd length the newest level
-    // is in u1 and the two arrays swap back.
-    for (int done = 0, blk = 0; done < nsteps; ++blk) {
-        int kb = min(k, nsteps - done);
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            if (a.out_step[q] > done && a.out_step[q] < done + kb) kb = a.out_step[q] - done;
-        gyw = gy0 + r0 + opaque_zero();
-        if (blk > 0) {
-            // publish the border band of the exact region (levels j and j-1):
-            // packed in LDS, then copied out with whole-line stores.  A row's
-            // block of the band and its offset there are uniform; a lane adds
-            // its column (top and bottom rows) or its place in the left and
-            // right column blocks (the rows between)
-            const int par = (blk - 1) & 1;
-            const int lside = lx < k ? lx : (OY - 2 * k) * k + lx - (OX - k);
+    // publish levels j and j-1 in slot `par`, read the halo from the
+    // neighbours' slots `par`, return slot `prev` to the empty pattern;
+    // false: a wait gave up
+    auto exchange = [&](int par, int prev) __attribute__((always_inline)) -> bool {
+        static_assert(2 * K <= 2 * R && K <= R, "halo rows lie in the first and last wave");
+        const int lane = lane_ + opaque_zero(), tid = wv * 64 + lane;
+        word *const out = mine + par * par_words;
+        // the border columns go through LDS, so that they leave in whole
+        // lines; the border rows, a line or more each, from registers
+        const bool side_l = lane >= K && lane < 2 * K, side_r = lane >= OX && lane < EX - K;
+        if (side_l || side_r) {
+            word *sb = stage + r0 * K + (side_l ? lane - K : K * EY + lane - OX);
 #pragma unroll
             for (int i = 0; i < R; ++i) {
-                const int ly = gyw + i - ey0;
-                if (ly < 0 || gyw + i >= ey1) continue;
-                if (ly < k || ly >= OY - k) {
-                    const int rb = (ly < k ? ly : ly - (OY - 2 * k)) * OX;
-                    if (xexact) {
-                        sband[rb + lx] = u0[i];
-                        sband[band + rb + lx] = u1[i];
-                    }
-                } else {
-                    const int sb = 2 * k * OX + (ly - k) * k;
-                    if (xband) {
-                        sband[sb + lside] = u0[i];
-                        sband[band + sb + lside] = u1[i];
-                    }
-                }
+                sb[i * K] = Wd::of(u0[i]);
+                sb[2 * K * EY + i * K] = Wd::of(u1[i]);
             }
-            __syncthreads();
-            T *const mine = shadow + ((int64_t)(par * ntl + tile) * 2) * band;
-            for (int t = threadIdx.x; t < 2 * band; t += 64 * W) st_coh(mine + t, sband[t]);
-            __builtin_amdgcn_s_waitcnt(0);   // the band stores are complete
-            __syncthreads();
-            if (threadIdx.x == 0) st_coh(flags + tile * TDP_RES_FLAG_STRIDE, blk);
-            // wait for the bands of the same block that this wave reads: its
-            // west and east neighbours', and those of the three tiles above
-            // (below) when it holds top (bottom) halo rows.  Across its waves
-            // the tile waits for all eight neighbours before the barrier after
-            // the halo loads, which is also where every wave sees an abort
-            {
-                const int l = lane, dy = l / 3 - 1;
-                const bool need = l < 9 && l != 4 &&
-                                  (dy == 0 || (dy < 0 ? r0 < k : r0 + R > k + OY));
-                const int nty = ty + dy, ntx = tx + l % 3 - 1;
-                if (need && (unsigned)nty < (unsigned)a.tiles_y && (unsigned)ntx < (unsigned)a.tiles_x) {
-                    const int *fp = flags + (nty * a.tiles_x + ntx) * TDP_RES_FLAG_STRIDE;
-                    int polls = 0;
-                    while (ld_coh(fp) < blk + a.wait_bias) {
-                        __builtin_amdgcn_s_sleep(2);   // back off: fewer coherent polls in flight
-                        if (++polls >= a.poll_limit || ld_coh(abort_word) != 0) {
-                            st_coh(abort_word, 1);
-                            s_abort = 1;
-                            break;
-                        }
-                    }
-                }
-            }
-            // the halo from the owners' bands: the owner's row and the part of
-            // the address it sets are uniform (counted along the rows, no
-            // division per row); a lane adds its owner's tile column and its
-            // column or place in the owner's left or right column block
-            int tyo = gyw >= 0 ? gyw / OY : -1, lyo = gyw - tyo * OY;
-            const T *const base = shadow + (int64_t)par * ntl * 2 * band;
-            const int ltile = txo * 2 * band;
-            const int lsideo = lxo < k ? lxo : (OY - 2 * k) * k + lxo - (OX - k);
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                const int r = r0 + i, gy = gyw + i;
-                const bool hrow = r < k || r >= k + OY;
-                if ((hrow || xhalo) && xin && (unsigned)gy < (unsigned)ny) {
-                    const bool full = lyo < k || lyo >= OY - k;
-                    const int ub = tyo * a.tiles_x * 2 * band +
-                                   (full ? (lyo < k ? lyo : lyo - (OY - 2 * k)) * OX
-                                         : 2 * k * OX + (lyo - k) * k);
-                    const T *src = base + ub + ltile + (full ? lxo : lsideo);
-                    u0[i] = ld_coh(src);
-                    u1[i] = ld_coh(src + band);
-                }
-                if (++lyo == OY) {
-                    lyo = 0;
-                    ++tyo;
-                }
-            }
-            c0[wf] = u0[0];
-            c0[wl] = u0[R - 1];
-            __syncthreads();
-            if (s_abort) return;     // a wait gave up: halo values may be stale
         }
-        bool odd = false;
+        // stores of the last exchange's emptied slot are complete before this
+        // exchange publishes
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        auto put_row = [&](int i, int at) __attribute__((always_inline)) {
+            st_coh(out + at * EX + lane, Wd::of(u0[i]));
+            st_coh(out + BAND + at * EX + lane, Wd::of(u1[i]));
+        };
+        // rows K .. 2K-1 and EY-2K .. EY-K-1 of the tile, in the first and
+        // last wave (and, where 2K > R, the ones beside them)
+        if (wv == 0) {
 #pragma unroll
-        for (int s = 0; s < kResKMax; s += 2) {
-            if (s >= kb) break;
-            res_step<T, SC, R>(c0, c1, rs, rn, wf, wl, fl, co, e, s2h, u0, u1,
-                               (T)fab[2 * (done + s)], (T)fab[2 * (done + s) + 1]);
-            __syncthreads();
-            if (s + 1 >= kb) {
-                odd = true;
+            for (int i = K; i < (2 * K < R ? 2 * K : R); ++i) put_row(i, i - K);
+        }
+        if (2 * K > R && wv == 1) {
+#pragma unroll
+            for (int i = 0; i < 2 * K - R; ++i) put_row(i, R + i - K);
+        }
+        if (wv == W - 1) {
+#pragma unroll
+            for (int i = (R > 2 * K ? R - 2 * K : 0); i < R - K; ++i) put_row(i, i - R + 3 * K);
+        }
+        if (2 * K > R && wv == W - 2) {
+#pragma unroll
+            for (int i = 2 * R - 2 * K; i < R; ++i) put_row(i, i - 2 * R + 3 * K);
+        }
+        {
+            constexpr int NS = 2 * K * EY, NT = 64 * W;           // words per level
+            word v[(2 * NS + NT - 1) / NT];
+#pragma unroll
+            for (int q = 0; q * NT < 2 * NS; ++q)
+                if (2 * NS % NT == 0 || q * NT + tid < 2 * NS) v[q] = stage[q * NT + tid];
+#pragma unroll
+            for (int q = 0; q * NT < 2 * NS; ++q) {
+                const int t = q * NT + tid;
+                if (2 * NS % NT == 0 || t < 2 * NS)
+                    st_coh(out + 2 * K * EX + t + (t >= NS ? BAND - NS : 0), v[q]);
+            }
+        }
+        __syncthreads();                                         // the staging is free
+
+        const word *const in = mine + par * par_words;
+        // whole halo rows: the south neighbour's last rows before its halo,
+        // the north one's first (their halo columns are replaced below)
+        const bool south = wv == 0 && nbS, north = wv == W - 1 && nbN;
+        const int64_t vstep = slot_words * a.tiles_x;
+        const word *const rowsrc = in + (south ? K * EX - vstep : vstep) + lane;
+        word t0[NQ], h0[K], h1[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) h0[i] = h1[i] = word(0);
+        // what has arrived is not read again; the abort word is looked at
+        // now and then (a read of it would double the time of a poll)
+        bool cols = false, rows = !(south || north);
+        for (int polls = 0;;) {
+            if (!cols) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+                    t0[q] = off[q] != INT32_MIN ? ld_coh(in + off[q]) : word(0);
+            }
+            if (!rows) {
+#pragma unroll
+                for (int i = 0; i < K; ++i) {
+                    h0[i] = ld_coh(rowsrc + i * EX);
+                    h1[i] = ld_coh(rowsrc + BAND + i * EX);
+                }
+            }
+            bool miss = a.wait_bias != 0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) miss |= t0[q] == Wd::empty;
+            cols = !__any(miss);
+            miss = a.wait_bias != 0;
+#pragma unroll
+            for (int i = 0; i < K; ++i) miss |= h0[i] == Wd::empty || h1[i] == Wd::empty;
+            rows = !__any(miss);
+            if (cols && rows) break;
+            ++polls;
+            if (polls >= a.poll_limit ||
+                (polls % 16 == 0 && __builtin_amdgcn_readfirstlane(ld_coh(abort_word)) != 0)) {
+                st_coh(abort_word, 1);
+                s_abort = 1;
                 break;
             }
-            res_step<T, SC, R>(c1, c0, rs, rn, wf, wl, fl, co, e, s2h, u1, u0,
-                               (T)fab[2 * (done + s + 1)], (T)fab[2 * (done + s + 1) + 1]);
+        }
+        if (south) {
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                u0[i] = Wd::value(h0[i]);
+                u1[i] = Wd::value(h1[i]);
+            }
+        }
+        if (north) {
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                u0[R - K + i] = Wd::value(h0[i]);
+                u1[R - K + i] = Wd::value(h1[i]);
+            }
+        }
+        // halo columns to their lanes, through the wave's part of the staging
+        word *const land = stage + wv * L::LAND;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            if (L::LAND % 64 == 0 || q * 64 + lane < L::LAND) land[q * 64 + lane] = t0[q];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if ((nbW && lane < K) || (nbE && lane >= EX - K)) {
+            const word *la = land + (lane < K ? lane : R * K + lane - (EX - K));
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                u0[i] = Wd::value(la[i * K]);
+                u1[i] = Wd::value(la[2 * R * K + i * K]);
+            }
+        }
+        c0[wf] = u0[0];
+        c0[wl] = u0[R - 1];
+        __syncthreads();
+        if (s_abort) return false;               // halo values may be missing
+        if (prev >= 0) {
+#pragma unroll
+            for (int q = 0; q * 64 * W < 2 * BAND; ++q) {
+                const int t = q * 64 * W + tid;
+                if (2 * BAND % (64 * W) == 0 || t < 2 * BAND)
+                    st_coh(mine + prev * par_words + t, word(Wd::empty));
+            }
+        }
+        return true;
+    };
+
+    // A run of steps ends at every sample step, so that samples are written
+    // outside the step loop; a run starts with an exchange (the first has its
+    // halo from the load) and has one every K steps.  Two steps a turn (the
+    // level arrays swap roles); after a run of odd length the newest level is
+    // in u1 and the two arrays swap back.
+    double ring = 0.0;
+    int par = 0, prev = -1;          // exchange slot (1, 2, 0, 1, ...) and the one before
+    for (int done = 0; done < nsteps;) {
+        int end = nsteps;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (a.out_step[q] > done && a.out_step[q] < end) end = a.out_step[q];
+        int left = done > 0 ? 0 : K;
+#pragma unroll 1
+        for (int j = done; j < end; j += 2, left -= 2) {
+            // the ring's other half: fetched half a round ahead, in place a turn ahead
+            if ((j >> 1 & 15) == 8 && threadIdx.x < 64) ring = tab[2 * ((j & ~31) + 32) + threadIdx.x];
+            if ((j >> 1 & 15) == 15 && threadIdx.x < 64)
+                ((double *)fab)[((j & 32) ^ 32) * 2 + threadIdx.x] = ring;
+            if (MULTI && left == 0) {
+                const int next = par == 2 ? 0 : par + 1;
+                if (!exchange(next, prev)) return;
+                prev = par = next;
+                left = K;
+            }
+            const double2 f0 = fab[j & 63];
+            res_step<T, SC, R>(c0, c1, rs, rn, wf, wl, fl, co, u0, u1, (T)f0.x, (T)f0.y);
+            __syncthreads();
+            if (j + 1 == end) break;
+            const double2 f1 = fab[j + 1 & 63];
+            res_step<T, SC, R>(c1, c0, rs, rn, wf, wl, fl, co, u1, u0, (T)f1.x, (T)f1.y);
             __syncthreads();
         }
-        if (odd) {
+        if ((end - done) & 1) {
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 const T t = u0[i];
                 u0[i] = u1[i];
                 u1[i] = t;
             }
+            if (!MULTI) {            // no exchange refreshes the edge rows
+                c0[wf] = u0[0];
+                c0[wl] = u0[R - 1];
+                __syncthreads();
+            }
         }
-        done += kb;
+        done = end;
         snapshot(done, u0);
     }
     T *u_out = (T *)a.u_out, *up_out = (T *)a.up_out;
+    if (u_out) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        if (exact_node(i)) {
-            const int64_t row = (int64_t)(gyw + i) * nx;
-            (u_out + row)[gx] = u0[i];
-            (up_out + row)[gx] = u1[i];
+        for (int i = 0; i < R; ++i) {
+            const int r = r0 + i, gy = gy0 + r;
+            if (xexact && r >= lo_row && r < hi_row && gy < ny) {
+                const int64_t row = (int64_t)gy * nx;
+                (u_out + row)[gx] = u0[i];
+                (up_out + row)[gx] = u1[i];
+            }
         }
     }
+}
+
+// Before a launch: every slot empty, the abort word (optionally) lowered.
+template <typename T>
+__global__ __launch_bounds__(256) void k_res_init(typename Word<T>::type *slots, int64_t n,
+                                                  int *abort_word, int clear)
+{
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *abort_word = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        slots[i] = Word<T>::empty;
+}
+
+// Behind a resident run on its stream, where the host does not wait for it:
+// returns at once unless the run gave up, else one workgroup redoes the whole
+// application from zero fields, one step after the other on fields in global
+// memory, and tells the host (host_word).  It is slow (a compute unit's rate)
+// and meant to be: its only task is that the call's result is always there.
+template <typename T>
+__global__ __launch_bounds__(1024) void k_res_recover(ResRecover a, Stencil<T> st)
+{
+    if (*a.abort_word == 0) return;
+    const int nx = a.nx, ny = a.ny;
+    const T *m = (const T *)a.m, *dn = (const T *)a.dn;
+    const double2 *F = (const double2 *)a.F;
+    for (int part = 0; part < a.parts; ++part) {
+        T *u = (T *)a.u0, *up = (T *)a.u1;
+        for (int64_t i = threadIdx.x; i < (int64_t)ny * nx; i += 1024) u[i] = up[i] = T(0);
+        __syncthreads();
+        for (int64_t j = 0; j < a.nsteps; ++j) {
+            const T fa = (T)a.tab[part][2 * j], fb = (T)a.tab[part][2 * j + 1];
+            double *o = j + 1 == a.out_step[0] ? a.out[part][0]
+                      : j + 1 == a.out_step[1] ? a.out[part][1] : nullptr;
+            for (int y = threadIdx.x >> 6; y < ny; y += 16)
+                for (int x = threadIdx.x & 63; x < nx; x += 64) {
+                    const int64_t i = (int64_t)y * nx + x;
+                    auto U = [&](int oy, int ox) -> T {
+                        return (unsigned)(y + oy) < (unsigned)ny && (unsigned)(x + ox) < (unsigned)nx
+                                   ? u[i + (int64_t)oy * nx + ox] : T(0);
+                    };
+                    const T *c = m + (int64_t)y * (nx + 1) + x;
+                    T co[6];
+                    fold_node<T, 3, 2, 6>(st, dn[i], c[0], c[1], c[nx + 1], c[nx + 2], co);
+                    T acc = co[0] * U(0, 0);
+                    acc += co[1] * U(0, -1);
+                    acc += co[2] * U(0, 1);
+                    acc += co[3] * U(-1, 0);
+                    acc += co[4] * U(1, 0);
+                    acc += co[5] * ((U(-1, -1) + U(-1, 1)) + (U(1, -1) + U(1, 1)));
+                    acc += fa * (dn[i] * (T)F[i].x);
+                    acc += fb * (dn[i] * (T)F[i].y);
+                    const T r = acc + (T(1) - T(2) * dn[i]) * up[i];
+                    up[i] = r;
+                    if (o) o[2 * i] = (double)r;
+                }
+            __syncthreads();       // one compute unit: its waves see each other's stores
+            T *t = u;
+            u = up;
+            up = t;
+        }
+    }
+    if (threadIdx.x == 0)
+        __hip_atomic_store(a.host_word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 }  // namespace
 
-int res_tile_rows(bool f64) { return (f64 ? kResR64 : kResR32) * kResW; }
+// tile shapes: rows per lane x waves (64 columns), FP64 / FP32
+//   0: 12 x 4 / 16 x 4, two workgroups per compute unit
+//   1:  8 x 8 / 8 x 8, for grids of one tile
+template <typename T>
+struct ResShape0;
+template <>
+struct ResShape0<double> {
+    static constexpr int R = 12, W = 4;
+};
+template <>
+struct ResShape0<float> {
+    static constexpr int R = 16, W = 4;
+};
 
-size_t res_band_bytes(bool f64)
+int res_tile_rows(bool f64, int shape)
 {
-    return f64 ? 2 * res_band_max(kResR64 * kResW) * sizeof(double)
-               : 2 * res_band_max(kResR32 * kResW) * sizeof(float);
+    return shape == 1 ? 64 : (f64 ? ResShape0<double>::R * ResShape0<double>::W
+                                  : ResShape0<float>::R * ResShape0<float>::W);
+}
+
+size_t res_slot_bytes(bool f64, int k)
+{
+    return 3 * 2 * (size_t)res_band(res_tile_rows(f64, 0), k) * (f64 ? sizeof(double) : sizeof(float));
 }
 
 int res_tiles(int ny, int nx, int k, bool f64, int *tiles_x, int *tiles_y)
 {
-    const int rows = res_tile_rows(f64);
-    if (rows == 0 || k < 2 || k > kResKMax || (k & 1) || 4 * k > rows) return 0;
-    const int ox = 64 - 2 * k, oy = rows - 2 * k;
-    const int tx = (nx + ox - 1) / ox, tyc = (ny + oy - 1) / oy;
+    if (k < 2 || k > 8 || (k & 1)) return 0;
+    if (ny <= res_tile_rows(f64, 1) && nx <= kResX) {      // one tile of either shape
+        if (tiles_x) *tiles_x = 1;
+        if (tiles_y) *tiles_y = 1;
+        return 1;
+    }
+    const int rows = res_tile_rows(f64, 0), ox = kResX - 2 * k, oy = rows - 2 * k;
+    // tile t covers 64 + t ox columns with the ones before it
+    const int tx = nx <= kResX ? 1 : 1 + (nx - kResX + ox - 1) / ox;
+    const int tyc = ny <= rows ? 1 : 1 + (ny - rows + oy - 1) / oy;
     if (tiles_x) *tiles_x = tx;
     if (tiles_y) *tiles_y = tyc;
-    return tx * tyc;
+    return (int64_t)tx * tyc > (1 << 20) ? (1 << 20) : tx * tyc;
 }
 
-template <typename T, int R>
-static hipError_t launch_res_t(const ResArgs &a, const Stencil<T> &st, hipStream_t s)
+template <typename T, int SC, int R, int W, int K, bool MULTI>
+static int res_per_cu()
 {
-    const int nt = a.tiles_x * a.tiles_y;
-    if (a.sc > 2)
-        hipLaunchKernelGGL((k_sweep2d_res<T, 3, R, kResW>), dim3(nt), dim3(64 * kResW), 0, s, a, st);
-    else
-        hipLaunchKernelGGL((k_sweep2d_res<T, 2, R, kResW>), dim3(nt), dim3(64 * kResW), 0, s, a, st);
+    static const int v = [] {
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep2d_res<T, SC, R, W, K, MULTI>,
+                                                         64 * W, 0) != hipSuccess)
+            nb = 0;
+        return nb;
+    }();
+    return v;
+}
+
+template <typename T, int SC>
+static int res_slots_sc(int k)
+{
+    constexpr int R = ResShape0<T>::R, W = ResShape0<T>::W;
+    switch (k) {
+    case 2: return res_per_cu<T, SC, R, W, 2, true>();
+    case 4: return res_per_cu<T, SC, R, W, 4, true>();
+    case 6: return res_per_cu<T, SC, R, W, 6, true>();
+    default: return res_per_cu<T, SC, R, W, 8, true>();
+    }
+}
+
+int res_workgroups_per_cu(int k, int sc, bool f64)
+{
+    if (f64) return sc > 2 ? res_slots_sc<double, 3>(k) : res_slots_sc<double, 2>(k);
+    return sc > 2 ? res_slots_sc<float, 3>(k) : res_slots_sc<float, 2>(k);
+}
+
+template <typename T, int SC>
+static hipError_t launch_res_sc(const ResArgs &a, const Stencil<T> &st, hipStream_t s)
+{
+    constexpr int R = ResShape0<T>::R, W = ResShape0<T>::W;
+    const int nt = a.tiles_x * a.tiles_y * a.parts;
+    if (a.tiles_x * a.tiles_y == 1) {
+        // one tile: 8 waves of 8 rows where 4 waves are not enough rows
+        if (a.ny <= R * W)
+            hipLaunchKernelGGL((k_sweep2d_res<T, SC, R, W, 8, false>), dim3(nt), dim3(64 * W), 0, s, a, st);
+        else
+            hipLaunchKernelGGL((k_sweep2d_res<T, SC, 8, 8, 8, false>), dim3(nt), dim3(512), 0, s, a, st);
+        return hipGetLastError();
+    }
+#define TDP_RES(K) \
+    hipLaunchKernelGGL((k_sweep2d_res<T, SC, R, W, K, true>), dim3(nt), dim3(64 * W), 0, s, a, st)
+    switch (a.k) {
+    case 2: TDP_RES(2); break;
+    case 4: TDP_RES(4); break;
+    case 6: TDP_RES(6); break;
+    default: TDP_RES(8); break;
+    }
+#undef TDP_RES
     return hipGetLastError();
 }
 
 hipError_t launch_sweep2d_res_f64(const ResArgs &a, const Stencil<double> &st, hipStream_t s)
 {
-    return launch_res_t<double, kResR64>(a, st, s);
+    return a.sc > 2 ? launch_res_sc<double, 3>(a, st, s) : launch_res_sc<double, 2>(a, st, s);
 }
 
 hipError_t launch_sweep2d_res_f32(const ResArgs &a, const Stencil<float> &st, hipStream_t s)
 {
-    return launch_res_t<float, kResR32>(a, st, s);
+    return a.sc > 2 ? launch_res_sc<float, 3>(a, st, s) : launch_res_sc<float, 2>(a, st, s);
+}
+
+hipError_t launch_res_recover(const ResRecover &a, const Stencil<double> &st,
+                              const Stencil<float> &st32, bool f64, hipStream_t s)
+{
+    if (f64)
+        hipLaunchKernelGGL(k_res_recover<double>, dim3(1), dim3(1024), 0, s, a, st);
+    else
+        hipLaunchKernelGGL(k_res_recover<float>, dim3(1), dim3(1024), 0, s, a, st32);
+    return hipGetLastError();
+}
+
+hipError_t launch_res_init(void *slots, size_t bytes, int *abort_word, bool clear, bool f64,
+                           hipStream_t s)
+{
+    const int64_t n = bytes / (f64 ? 8 : 4);
+    const int grid = (int)std::min<int64_t>((n + 1023) / 1024, 2048);
+    if (f64)
+        hipLaunchKernelGGL(k_res_init<double>, dim3(grid), dim3(256), 0, s,
+                           (unsigned long long *)slots, n, abort_word, clear ? 1 : 0);
+    else
+        hipLaunchKernelGGL(k_res_init<float>, dim3(grid), dim3(256), 0, s, (unsigned *)slots, n,
+                           abort_word, clear ? 1 : 0);
+    return hipGetLastError();
 }
 
 }  // namespace tdp

@@ -188,32 +188,54 @@ bool abd_tile_ok(int shape, bool f64);    // tile shapes of the blocked I_abd ke
 
 // Resident-tile 2-D sweep (sweep_res.hip): one workgroup per tile keeps its
 // tile in registers for a whole run of steps and swaps k-wide halo bands with
-// the neighbouring tiles through `shadow` every k steps.  Every tile must be
-// resident at once (tiles <= compute units); a wait that does not end sets
-// the abort word and the launch ends early with that status.
-#define TDP_RES_MAXSTEPS 1024   // steps of one launch (forcing scalars staged in LDS)
-#define TDP_RES_FLAG_STRIDE 32  // ints between tile flags (one 128-byte line each)
+// the neighbouring tiles through `slots` every k steps.  Every workgroup must
+// be resident at once (workgroups <= compute units x res_workgroups_per_cu,
+// one launch at a time); a wait that does not end sets the abort word and the
+// launch ends early with that status.  A grid of one tile and one part waits
+// for nothing and needs no slots.
+#define TDP_RES_MAXSTEPS 4096   // steps of one launch
 struct ResArgs {
     int ny, nx;
     int sc;
     int k;                      // steps between exchanges: 2, 4, 6 or 8
     int nsteps;                 // steps of this launch, 1..TDP_RES_MAXSTEPS
     int tiles_x, tiles_y;
-    const void *u_in, *up_in;   // u_j, u_{j-1}
-    void *u_out, *up_out;       // u_{j+nsteps}, u_{j+nsteps-1} (distinct from the inputs)
-    const void *m, *dn, *F;
-    const double *tab;          // (fa, fb) of the launch's steps
-    int out_step[2];            // 1-based step whose field goes to out[i] (0: none)
-    double *out[2];             // stride-2 outputs (complex128 real or imaginary part)
-    void *shadow;               // [2 parities][tiles][2 levels][band] exchange buffer
-    int *flags;                 // tiles x TDP_RES_FLAG_STRIDE ints, then the abort word
-    int poll_limit;             // flag polls before a wait gives up
-    int wait_bias;              // added to the awaited flag value (0; > 0 forces the abort path)
+    int parts;                  // real fields advanced side by side (1, or 2: Definition 4)
+    const void *u_in, *up_in;   // u_j, u_{j-1}; null: both zero (parts 1 only when given)
+    void *u_out, *up_out;       // u_{j+nsteps}, u_{j+nsteps-1} (distinct from the inputs), or null
+    const void *m, *dn;
+    const void *F;              // complex128
+    const double *tab[2];       // per part: (fa, fb) of the launch's steps
+    int out_step[2];            // 1-based step whose field goes to out[part][i] (0: none)
+    double *out[2][2];          // stride-2 outputs (complex128 real or imaginary part)
+    void *slots;                // exchange buffer: [3][workgroups][2 levels][band]
+    int *abort_word;
+    int poll_limit;             // polls before a wait gives up
+    int wait_bias;              // 1: no poll succeeds (forces the abort path)
 };
 hipError_t launch_sweep2d_res_f64(const ResArgs &a, const Stencil<double> &st, hipStream_t s);
 hipError_t launch_sweep2d_res_f32(const ResArgs &a, const Stencil<float> &st, hipStream_t s);
-int res_tile_rows(bool f64);      // extended tile rows (64 columns)
-size_t res_band_bytes(bool f64);  // exchange-buffer bytes per tile and parity (largest depth)
+// every slot word of `bytes` to the empty pattern, the abort word to 0 if clear
+hipError_t launch_res_init(void *slots, size_t bytes, int *abort_word, bool clear, bool f64,
+                           hipStream_t s);
+// The application of a resident run that gave up, redone behind it on the
+// stream (one workgroup; does nothing when the abort word is 0).
+struct ResRecover {
+    int ny, nx, parts;
+    int64_t nsteps;             // the whole application
+    int64_t out_step[2];
+    void *u0, *u1;              // field planes
+    const void *m, *dn, *F;
+    const double *tab[2];
+    double *out[2][2];
+    const int *abort_word;
+    int *host_word;             // pinned: raised when the recovery ran
+};
+hipError_t launch_res_recover(const ResRecover &a, const Stencil<double> &st,
+                              const Stencil<float> &st32, bool f64, hipStream_t s);
+int res_tile_rows(bool f64, int shape);
+size_t res_slot_bytes(bool f64, int k);   // exchange-buffer bytes per workgroup
+int res_workgroups_per_cu(int k, int sc, bool f64);   // queried once; call before any capture
 // tiles of the resident grid at exchange depth k (0 if k is not supported)
 int res_tiles(int ny, int nx, int k, bool f64, int *tiles_x, int *tiles_y);
 
@@ -427,14 +449,16 @@ struct tdp_op {
     void *Ustage = nullptr;    // complex128 output of the captured loop
     double *gcell = nullptr;   // per-cell gradient scratch
     // resident-tile sweep (kernel 5): compute units of the device, the
-    // exchange planes and tile flags, device copies of the forcing tables,
-    // a pinned mirror of the abort word
+    // exchange slots, the abort word and its pinned mirror, device copies of
+    // the forcing tables
     int ncu = 0;
-    void *res_shadow = nullptr;
-    int *res_flags = nullptr;
-    int res_ntiles = 0;                    // tiles the flag array holds
+    void *res_slots = nullptr;
+    size_t res_slots_bytes = 0;
+    int *res_abort = nullptr;
+    uint64_t res_id = 0;                   // this op among the process's resident launches
     int res_aborts = 0;                    // resident launches redone with the blocked sweep
+    bool res_off = false;                  // after an abort: the automatic choice leaves kernel 5 out
     bool res_force_abort = false;          // test hook: every resident wait gives up
-    int *res_host = nullptr;
+    int *res_host = nullptr;               // pinned: [0] the abort word, [1] raised by a recovery
     std::map<std::tuple<int, double, int>, double *> dtables;
 };
