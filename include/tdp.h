@@ -274,7 +274,7 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               blocked 2-D sweep on tile 5 (FP64) or 8 (FP32) at depth 8, with
  *               the cell damping on tile 7 (FP64) or 4 (FP32); in 3-D the
  *               two-step streamed sweep for tables without corner entries
- *               (FP64 tile 1; FP32 tile 2, tile 1 below 3 * 2^20 nodes) and
+ *               (FP64 tile 1; FP32 tile 2, tile 0 below 3 * 2^20 nodes) and
  *               the one-step streamed sweep on tile 0 otherwise; tb_depth and
  *               tile ignored),
  *               1 one step per launch, 2 temporally blocked (2-D; with the
@@ -303,7 +303,8 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               kernel 5: steps between halo exchanges, 2, 4, 6 or 8 (0: 4);
  *               kernel 3: planes per chunk (0 auto: 32, halved down
  *               to 8 until the launch has about 8192 waves); kernel 4: the
- *               fewest planes per workgroup run (0: 8; the launch is one
+ *               fewest planes per workgroup run (0: 2, with corner entries
+ *               8; the launch is one
  *               round of resident workgroups sharing the (column block,
  *               plane) units equally, so this only limits how finely a
  *               small grid is split)
@@ -316,8 +317,10 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               6 64x64 (8 x 8), 7 32x64 (2 x 16), 8 128x64 (8 x 16, FP32 only);
  *               kernel 3: 0 8x64 columns (4 waves x 2
  *               rows each), 1 16x64 (4 waves x 4 rows), 2 16x64 (8 x 2);
- *               kernel 4: level 1 on a 66-wide block with a one-node rim,
- *               level 2 (the output) on its interior: 0 66x15 on 512
+ *               kernel 4: tables without corner entries: rows in registers,
+ *               FP64 on 16x64 blocks whatever the tile, FP32 0 16x64, 1 and 2
+ *               32x64; others: level 1 on a 66-wide block with a one-node
+ *               rim, level 2 (the output) on its interior: 0 66x15 on 512
  *               threads (two nodes each, output 13x64), 1 66x15 on 1024
  *               threads (one node each), 2 66x31 on 1024 threads (output
  *               29x64; FP32 only, FP64 runs shape 1)                      */
@@ -343,7 +346,7 @@ int tdp_op_force_resident_abort(tdp_op *op, int on);
  * 8 for the 2-D Table 1 loop; the blocked I_abd tiles
  * x depths 2, 3, 4, 6, 8 with the 2-D cell damping; in 3-D the one-step
  * streamed shapes x chunk lengths 4, 8, 16, 32, 64 and the two-step shapes x
- * shortest runs 8 and 32) over
+ * shortest runs 2, 8 and 32) over
  * periods_T periods with HIP events on the op's stream, and makes
  * the fastest the op's tuning.  best (host, may be NULL) receives it; table
  * (host, may be NULL) receives up to cap rows of {kernel, tb_depth, tile,

@@ -615,15 +615,17 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             k = 8;
             t = f64 ? 5 : 8;
         } else if (op->sc <= 3 && op->mc <= 2) {
-            // 3-D compact tables: two steps per launch, FP64 on 66 x 15
-            // blocks, FP32 on 66 x 31 blocks (66 x 15 below about 3 * 2^20
-            // nodes).  Measured per step against the one-step sweep: FP64
-            // 17.9 / 23.4 us at 128^3, 73 / 81 at 192^3, 132 / 146 at 256^3;
-            // FP32 14.3 / 17.5 at 128^3, 41 / 49 at 192^3, 77 / 84 at 224^3,
-            // but 82 / 79 at 256^3 (the autotuner decides there)
+            // 3-D tables without corner entries: two steps per launch with
+            // the rows in registers.  FP32 on tiles of 16 rows below about
+            // 3 * 2^20 nodes, where workgroups are few, else of 32, a
+            // smaller part of which is halo: 5.2 against 6.5 us per step at
+            // 64^3, 12.2 / 12.5 at 128^3, 77 / 72 at 256^3.  Runs down to two
+            // planes, so that a small grid still fills the chip: 64^3 FP64
+            // 6.7 us per step, 10.4 with runs of at least eight (grids that
+            // fill it with longer runs get those anyway)
             kern = 4;
-            k = 8;
-            t = f64 || op->N < (3 << 20) ? 1 : 2;
+            k = 2;
+            t = f64 ? 1 : (op->N < (3 << 20) ? 0 : 2);
         } else {
             kern = 3;
             k = t = 0;
@@ -646,11 +648,16 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
         if (4 * k > rows || 4 * k > tb2d_tile_cols(t)) k = rows / 8;   // keep at least half the tile exact
     } else if (kern == 3 || kern == 4) {
         if (t > 2) t = 1;
+        // rows too long for the register form's 32-bit offsets: one step per launch
+        if (kern == 4 && op->sc <= 3 && op->mc <= 2 && !sweep3d_reg2_applies(op->n, op->sc, op->mc)) {
+            kern = 3;
+            k = 0;
+        }
         if (k == 0 && kern == 4) {
             // fewest planes per workgroup run: the run count per column block
             // is chosen to fill whole rounds of the resident workgroups, so
             // this only bounds how finely a small grid is split
-            k = 8;
+            k = op->sc > 3 || op->mc > 2 ? 8 : 2;
         } else if (k == 0) {
             // default chunk length: halve from 32 (down to 8) until the launch
             // has about 8192 waves, so that small grids still fill the chip
@@ -1010,10 +1017,11 @@ static int issue_steps_3d2(tdp_op *op, const LoopBufs &lb, int T, double rho, in
         b.F = Fin;
         b.out = out_for(j + 1);
         if (f64)
-            TDP_CHECK_HIP(launch_sweep3d_stream_f64(b, op->st_step, tab.a(j), tab.b(j), shape, zc, s));
+            TDP_CHECK_HIP(launch_sweep3d_stream_f64(b, op->st_step, tab.a(j), tab.b(j), shape,
+                                                    std::max(zc, 8), s));
         else
             TDP_CHECK_HIP(launch_sweep3d_stream_f32(b, op->st_step32, (float)tab.a(j),
-                                                    (float)tab.b(j), shape, zc, s));
+                                                    (float)tab.b(j), shape, std::max(zc, 8), s));
     }
     return TDP_OK;
 }
@@ -1376,10 +1384,13 @@ extern "C" int tdp_op_autotune(tdp_op *op, int periods_T, double rho, int varian
         for (int shape = 0; shape < 3; ++shape)
             for (int zc : {4, 8, 16, 32, 64}) cand.push_back({3, zc, 1, shape});
         // two-step kernel: the depth is only the fewest planes per workgroup
-        // run (it matters on small grids); FP64 runs shape 2 as shape 1
+        // run (it matters on small grids).  FP64 runs shape 2 as shape 1; of
+        // the register form it has one shape, FP32 two (0 and 2)
+        const bool corners = op->sc > 3 || op->mc > 2;
         for (int shape = 0; shape < 3; ++shape) {
             if (shape == 2 && op->prec == TDP_F64) continue;
-            for (int zc : {8, 32}) cand.push_back({4, zc, 1, shape});
+            if (!corners && shape == (op->prec == TDP_F64 ? 0 : 1)) continue;
+            for (int zc : {2, 8, 32}) cand.push_back({4, zc, 1, shape});
         }
     }
     const tdp_tuning saved = op->tune;

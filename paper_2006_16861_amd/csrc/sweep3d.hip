@@ -82,15 +82,6 @@ struct Fold3 {
     T c0, cw, ce, cs, cn, cd, cu, d;
 };
 
-// Compact form, for a fold kept in registers until a later update: two
-// opposite faces share the node's eight cells between them, so their
-// coefficients sum to the same cx = d (2 s_1 + m_1 sum w) on every axis.  It
-// keeps the west, south and down coefficients and cx (east = cx - west, ...).
-template <typename T>
-struct Fold3c {
-    T c0, cx, cw, cs, cd, d;
-};
-
 template <typename T>
 struct CellSums {
     T w0, ww, ws, wd, wu;     // all eight cells; those with ex = 0, ey = 0, ez = 0, ez = 1
@@ -125,20 +116,6 @@ __device__ __forceinline__ Fold3<T> fold3(const T (&w)[8], T d, const Stencil<T>
     return f;
 }
 
-template <typename T>
-__device__ __forceinline__ Fold3c<T> fold3c(const T (&w)[8], T d, const Stencil<T> &st)
-{
-    const CellSums<T> c = cell_sums(w);
-    Fold3c<T> f;
-    f.c0 = d * (st.c0 + st.m[0] * c.w0);
-    f.cx = d * (T(2) * st.s[1] + st.m[1] * c.w0);
-    f.cw = d * (st.s[1] + st.m[1] * c.ww);
-    f.cs = d * (st.s[1] + st.m[1] * c.ws);
-    f.cd = d * (st.s[1] + st.m[1] * c.wd);
-    f.d = d;
-    return f;
-}
-
 template <typename T, typename LoadU>
 __device__ __forceinline__ T edge_sum(const LoadU &U)
 {
@@ -160,24 +137,6 @@ __device__ __forceinline__ T update3(const LoadU &U, const Fold3<T> &f, const St
     acc += f.cn * U(0, 1, 0);
     acc += f.cd * U(-1, 0, 0);
     acc += f.cu * U(1, 0, 0);
-    acc += (f.d * st.s[2]) * edges;
-    acc += fa * dfr;
-    acc += fb * dfi;
-    return acc + (T(1) - T(2) * f.d) * uprev;
-}
-
-template <typename T, typename LoadU>
-__device__ __forceinline__ T update3(const LoadU &U, const Fold3c<T> &f, const Stencil<T> &st,
-                                     T fa, T fb, T dfr, T dfi, T uprev)
-{
-    const T edges = edge_sum<T>(U);
-    T acc = f.c0 * U(0, 0, 0);
-    acc += f.cw * U(0, 0, -1);
-    acc += (f.cx - f.cw) * U(0, 0, 1);
-    acc += f.cs * U(0, -1, 0);
-    acc += (f.cx - f.cs) * U(0, 1, 0);
-    acc += f.cd * U(-1, 0, 0);
-    acc += (f.cx - f.cd) * U(1, 0, 0);
     acc += (f.d * st.s[2]) * edges;
     acc += fa * dfr;
     acc += fb * dfi;
@@ -336,7 +295,8 @@ __global__ __launch_bounds__(64 * TY) void k_sweep3d_stream(
     }
 }
 
-// Two steps per launch.  From u_j (level 0) and u_{j-1}, a workgroup computes
+// Two steps per launch, for tables with corner entries (sweep3d_reg.hip has
+// the others).  From u_j (level 0) and u_{j-1}, a workgroup computes
 // level 1 (u_{j+1}) on a 66 x LY node block and level 2 (u_{j+2}) on its
 // 64 x (LY-2) interior, walking along axis 0: in iteration i it forms level 1
 // on plane a = zb-1+i and level 2 on plane a-2, whose level-1 inputs (planes
@@ -346,10 +306,8 @@ __global__ __launch_bounds__(64 * TY) void k_sweep3d_stream(
 // level-1 row and a 256-node axis takes exactly four column blocks.  LDS
 // rings: level-0 planes in 5 slots (a-2 .. a+1 read, a+2 arriving from the
 // registers it was prefetched into), level-1 planes in 4 (a written, a-3 ..
-// a-1 read), cell planes in 3 (5 when level 2 refolds from the cells).  u_{j-1},
-// d and F of plane a are fetched one iteration ahead.  For the compact tables a
-// node's coefficients are folded once, at level 1, and carried in registers to
-// its level-2 update two iterations later.  Per node and launch this reads
+// a-1 read), cell planes in 5.  u_{j-1}, d and F of plane a are fetched one
+// iteration ahead, and d and F carried to level 2.  Per node and launch this reads
 // u_j, u_{j-1}, m, d, F once and writes u_{j+1}, u_{j+2}: about 4 words per
 // node-step instead of 7.
 //
@@ -366,7 +324,7 @@ __global__ __launch_bounds__(64 * TY) void k_sweep3d_stream(
 template <typename T, int NT>
 constexpr int stream2_waves() { return NT >= 1024 || sizeof(T) == 4 ? 4 : 2; }
 
-template <typename T, int SC, int MC, int NT, int LY, bool NTS>
+template <typename T, int NT, int LY, bool NTS>
 __global__ __launch_bounds__(NT, (stream2_waves<T, NT>())) void k_sweep3d_stream2(
     const T *__restrict__ u, const T *__restrict__ up, T *__restrict__ u2o,
     T *__restrict__ u1o, const T *__restrict__ m, const T *__restrict__ dn,
@@ -380,8 +338,7 @@ __global__ __launch_bounds__(NT, (stream2_waves<T, NT>())) void k_sweep3d_stream
     constexpr int EX = LX + 2, NE = EX * (LY + 2);  // level-0 plane with its halo
     constexpr int CX = LX + 1, NC = CX * (LY + 1);  // cell plane
     constexpr int UPT = (NE + NT - 1) / NT, CPT = (NC + NT - 1) / NT;
-    constexpr bool FOLD = SC == 3 && MC == 2;
-    constexpr int NCS = FOLD ? 3 : 5;
+    constexpr int NCS = 5;
     __shared__ T s0[5][NE];
     __shared__ T s1[4][NL];
     __shared__ T scl[NCS][NC];
@@ -410,14 +367,12 @@ __global__ __launch_bounds__(NT, (stream2_waves<T, NT>())) void k_sweep3d_stream
     T ru[UPT], rc[CPT];
     int eo[UPT], co[CPT], no[P];   // in-plane offsets from the block origin, -1 outside
     T cum[P], cd[P], cfr[P], cfi[P];
-    // what a node's level-2 update needs from its plane: the folded
-    // coefficients with d, and d F (unfolded tables: d and F).  Three sets:
+    // what a node's level-2 update needs from its plane.  Three sets:
     // iteration i writes set i mod 3 (plane a) and reads set (i + 1) mod 3
     // (plane a-2, written two iterations earlier); the loop is unrolled by
     // three so that the sets stay in place
     struct Carry {
-        Fold3c<T> f;
-        T fr, fi;
+        T d, fr, fi;
     };
     Carry kA[P], kB[P], kC[P];
 
@@ -533,18 +488,11 @@ __global__ __launch_bounds__(NT, (stream2_waves<T, NT>())) void k_sweep3d_stream
                         const int ex = e & 1, ey = (e >> 1) & 1, ez = (e >> 2) & 1;
                         w[e] = (ez ? c1p : c0p)[cb(q) + ey * CX + ex];
                     }
-                    if constexpr (FOLD) {
-                        k0[q].f = fold3c(w, cd[q], st);
-                        k0[q].fr = cd[q] * cfr[q];
-                        k0[q].fi = cd[q] * cfi[q];
-                        v = update3(U, k0[q].f, st, fa1, fb1, k0[q].fr, k0[q].fi, cum[q]);
-                    } else {
-                        const T acc = stencil27<SC, MC>(U, w, st);
-                        v = cd[q] * (acc + fa1 * cfr[q] + fb1 * cfi[q]) - (T(2) * cd[q] - T(1)) * cum[q];
-                        k0[q].f.d = cd[q];
-                        k0[q].fr = cfr[q];
-                        k0[q].fi = cfi[q];
-                    }
+                    const T acc = stencil27<4, 4>(U, w, st);
+                    v = cd[q] * (acc + fa1 * cfr[q] + fb1 * cfi[q]) - (T(2) * cd[q] - T(1)) * cum[q];
+                    k0[q].d = cd[q];
+                    k0[q].fr = cfr[q];
+                    k0[q].fi = cfi[q];
                     if (aout && inner(q)) {
                         const int64_t i = a * plane + nb + no[q];
                         stnt<NTS>(v, u1o + i);
@@ -569,21 +517,16 @@ __global__ __launch_bounds__(NT, (stream2_waves<T, NT>())) void k_sweep3d_stream
                     return pl[base + oy * LX + ox];
                 };
                 const T uc = u0c[ub(q)];
-                T v;
-                if constexpr (FOLD) {
-                    v = update3(U, k2[q].f, st, fa2, fb2, k2[q].fr, k2[q].fi, uc);
-                } else {
-                    const T *d0p = scl[cslot(b)], *d1p = scl[cslot(b + 1)];
-                    T w[8];
+                const T *d0p = scl[cslot(b)], *d1p = scl[cslot(b + 1)];
+                T w[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int ex = e & 1, ey = (e >> 1) & 1, ez = (e >> 2) & 1;
-                        w[e] = (ez ? d1p : d0p)[cb(q) + ey * CX + ex];
-                    }
-                    const T acc = stencil27<SC, MC>(U, w, st);
-                    const T d2 = k2[q].f.d;
-                    v = d2 * (acc + fa2 * k2[q].fr + fb2 * k2[q].fi) - (T(2) * d2 - T(1)) * uc;
+                for (int e = 0; e < 8; ++e) {
+                    const int ex = e & 1, ey = (e >> 1) & 1, ez = (e >> 2) & 1;
+                    w[e] = (ez ? d1p : d0p)[cb(q) + ey * CX + ex];
                 }
+                const T acc = stencil27<4, 4>(U, w, st);
+                const T d2 = k2[q].d;
+                const T v = d2 * (acc + fa2 * k2[q].fr + fb2 * k2[q].fi) - (T(2) * d2 - T(1)) * uc;
                 const int64_t i = b * plane + nb + no[q];
                 stnt<NTS>(v, u2o + i);
                 if (out2) out2[2 * i] = (double)v;
@@ -609,13 +552,13 @@ __global__ __launch_bounds__(NT, (stream2_waves<T, NT>())) void k_sweep3d_stream
 
 // workgroups of one stream2 instantiation resident per compute unit, queried
 // once (sweep3d_stream2_prepare runs the query before any stream capture)
-template <typename T, int SC, int MC, int NT, int LY, bool NTS>
+template <typename T, int NT, int LY, bool NTS>
 static int stream2_per_cu()
 {
     static const int v = [] {
         int nb = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &nb, k_sweep3d_stream2<T, SC, MC, NT, LY, NTS>, NT, 0) != hipSuccess || nb < 1)
+                &nb, k_sweep3d_stream2<T, NT, LY, NTS>, NT, 0) != hipSuccess || nb < 1)
             nb = 1;
         return nb;
     }();
@@ -625,18 +568,15 @@ static int stream2_per_cu()
 template <typename T, int NT, int LY>
 static void prepare_stream2_t()
 {
-    stream2_per_cu<T, 3, 2, NT, LY, true>();
-    stream2_per_cu<T, 3, 2, NT, LY, false>();
-    stream2_per_cu<T, 4, 4, NT, LY, true>();
-    stream2_per_cu<T, 4, 4, NT, LY, false>();
+    stream2_per_cu<T, NT, LY, true>();
+    stream2_per_cu<T, NT, LY, false>();
 }
 
 // Runs per column block: the one minimising rounds x (run length + 3), the
 // rounds of `slots` resident workgroups that ncb x nrun workgroups take and
 // the prologue of about three planes' loads per run; runs of at least zc
-// planes.  256^3 FP32 on shape 2 (36 blocks, 256 slots): 7 runs of 36-37
-// planes, one round.
-static int stream2_runs(int64_t ncb, int nz, int zc, int64_t slots)
+// planes.
+int stream2_runs(int64_t ncb, int nz, int zc, int64_t slots)
 {
     const int kmax = std::max(1, std::min(4096, nz / std::max(zc, 1)));
     int best_k = 1;
@@ -666,33 +606,29 @@ static hipError_t launch_stream2_t(const Stream2Args &a, const Stencil<T> &st, h
     const T fa1 = (T)a.fa[0], fb1 = (T)a.fb[0], fa2 = (T)a.fa[1], fb2 = (T)a.fb[1];
     const bool nt = stream_nt((int64_t)7 * sizeof(T) * nz * ny * nx);
     if (ncb * nz > ((int64_t)1 << 31) - 1) return hipErrorInvalidValue;
-#define TDP_S2(SC, MC, NTS)                                                                          \
+#define TDP_S2(NTS)                                                                          \
     do {                                                                                             \
-        const int64_t slots = (int64_t)stream2_per_cu<T, SC, MC, NT, LY, NTS>() * a.ncu;             \
+        const int64_t slots = (int64_t)stream2_per_cu<T, NT, LY, NTS>() * a.ncu;             \
         const int nrun = stream2_runs(ncb, nz, a.zc, std::max<int64_t>(slots, 1));                   \
         const int per_xcd = (int)((ncb * nrun + 7) / 8);                                             \
-        hipLaunchKernelGGL((k_sweep3d_stream2<T, SC, MC, NT, LY, NTS>), dim3(8 * per_xcd), dim3(NT), \
+        hipLaunchKernelGGL((k_sweep3d_stream2<T, NT, LY, NTS>), dim3(8 * per_xcd), dim3(NT), \
                            0, s, u, up, u2o, u1o, m, dn, F, nz, ny, nx, st, fa1, fb1, fa2, fb2,      \
                            a.out1, a.out2, tiles_x, (int)ncb, nrun, per_xcd);                        \
     } while (0)
-    if (a.sc <= 3 && a.mc <= 2) {
-        if (nt) TDP_S2(3, 2, true);
-        else TDP_S2(3, 2, false);
-    } else {
-        if (nt) TDP_S2(4, 4, true);
-        else TDP_S2(4, 4, false);
-    }
+    if (nt) TDP_S2(true);
+    else TDP_S2(false);
 #undef TDP_S2
     return hipGetLastError();
 }
 
-// shape: 0 -> 512 threads on a 66 x 15 level-1 block (64 x 13 outputs, two
+// Tables without corner entries go to the register form.  shape: 0 -> 512 threads on a 66 x 15 level-1 block (64 x 13 outputs, two
 // positions per thread), 1 -> 1024 threads on 66 x 15 (one position per
 // thread), 2 -> 1024 threads on 66 x 31 (64 x 29 outputs; FP32 only, FP64
 // takes shape 1: its LDS rings would exceed 160 KB)
 hipError_t launch_sweep3d_stream2_f64(const Stream2Args &a, const Stencil<double> &st, int shape,
                                       hipStream_t s)
 {
+    if (a.sc <= 3 && a.mc <= 2) return launch_sweep3d_reg2_f64(a, st, s);
     switch (shape) {
     case 0: return launch_stream2_t<double, 512, 15>(a, st, s);
     default: return launch_stream2_t<double, 1024, 15>(a, st, s);
@@ -702,6 +638,7 @@ hipError_t launch_sweep3d_stream2_f64(const Stream2Args &a, const Stencil<double
 hipError_t launch_sweep3d_stream2_f32(const Stream2Args &a, const Stencil<float> &st, int shape,
                                       hipStream_t s)
 {
+    if (a.sc <= 3 && a.mc <= 2) return launch_sweep3d_reg2_f32(a, st, shape, s);
     switch (shape) {
     case 0: return launch_stream2_t<float, 512, 15>(a, st, s);
     case 2: return launch_stream2_t<float, 1024, 31>(a, st, s);
@@ -711,6 +648,7 @@ hipError_t launch_sweep3d_stream2_f32(const Stream2Args &a, const Stencil<float>
 
 void sweep3d_stream2_prepare(bool f64, int shape)
 {
+    sweep3d_reg2_prepare(f64);
     if (f64) {
         switch (shape) {
         case 0: prepare_stream2_t<double, 512, 15>(); break;

@@ -268,6 +268,15 @@ hipError_t launch_sweep3d_stream2_f32(const Stream2Args &a, const Stencil<float>
                                       hipStream_t s);
 // queries the residency of the shape's kernels (call before any stream capture)
 void sweep3d_stream2_prepare(bool f64, int shape);
+// the same with the rows in registers (sweep3d_reg.hip), for the tables without
+// corner entries; n: the grid's nodes per axis
+bool sweep3d_reg2_applies(const int *n, int sc, int mc);
+hipError_t launch_sweep3d_reg2_f64(const Stream2Args &a, const Stencil<double> &st, hipStream_t s);
+hipError_t launch_sweep3d_reg2_f32(const Stream2Args &a, const Stencil<float> &st, int shape,
+                                   hipStream_t s);
+void sweep3d_reg2_prepare(bool f64);
+// runs of at least zc planes per column block that fill whole rounds of `slots`
+int stream2_runs(int64_t ncb, int nz, int zc, int64_t slots);
 
 // complex-linear variant: u, up are complex fields (re, im pairs of T); `out`
 // (if non-null) receives u_{j+1} as complex128.
