@@ -283,7 +283,8 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               variant), 4 streamed along axis 0 with two steps per launch
  *               (3-D, Table 1 variant), 5 resident tiles (2-D, node
  *               damping, tables without corner mass entries: each tile,
- *               48x64 in FP64 and 64x64 in FP32, two to a compute unit, stays
+ *               48x64 in FP64 and 64x64 in FP32, two to a compute unit, or
+ *               32x64 where one of them per compute unit is enough, stays
  *               on chip for up to 4096 steps per launch and swaps k-wide halo
  *               bands with its neighbours through global memory every k steps;
  *               the tiles must all be resident at once, so the resident

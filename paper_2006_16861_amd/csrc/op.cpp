@@ -552,22 +552,31 @@ static int ensure_complex_fields(tdp_op *op)
 // grids whose tiles are resident all at once; elsewhere, and with resident =
 // false (the allocation-free entry point, a stream under capture), the plan
 // falls back to the blocked sweep.
+// The tile shape of a run: the 32-row one where its tiles take a compute unit each.
+static int res_shape(const tdp_op *op, int k, int parts)
+{
+    const bool f64 = op->prec == TDP_F64;
+    return (int64_t)parts * res_tiles(op->n[0], op->n[1], k, f64, 2, nullptr, nullptr) <= op->ncu ? 2 : 0;
+}
+
 static bool res_applies(const tdp_op *op, int k, int parts)
 {
     if (op->ndim != 2 || op->dform != TDP_DAMP_NODE || op->mc > 2) return false;
     const bool f64 = op->prec == TDP_F64;
-    const int64_t nt = res_tiles(op->n[0], op->n[1], k, f64, nullptr, nullptr);
+    const int64_t nt = res_tiles(op->n[0], op->n[1], k, f64, res_shape(op, k, parts), nullptr, nullptr);
     if (nt <= 0) return false;
     return nt == 1 || nt * parts <= (int64_t)op->ncu * res_workgroups_per_cu(k, op->sc, f64);
 }
 
 // The automatic choice's exchange depth, 0 where the resident sweep does not
-// apply.  Model, measured per block of k steps (us): 2.5 for the exchange and
-// 0.6 a step with one workgroup per compute unit; 3 and 0.85 with two, which
-// share its vector units (256^2 FP64: 1.16 us a step at depth 4, 1.01 at depth
-// 8; 1024^2, 494 workgroups: 1.55 at depth 4, the deepest that fits).  The
-// blocked sweep takes 1.05 us a step on the smallest grids (a launch per 8
-// steps) and 3.0 at 1024^2, so the resident one is chosen wherever it fits.
+// apply.  Model, measured per block of k steps (us): 1.4 for the exchange and
+// 0.5 a step on 32-row tiles (300^2 FP64: 0.89 us a step at depth 4, 0.745 at
+// 8); 1.35 and 0.7 on the others with one workgroup per compute unit (512^2: 0.95
+// at depth 6); 3 and 0.85 with two, which share its vector units (700^2: 1.10 at
+// depth 4 with one each, 1.43 at depth 8 with two; 1024^2, 494 workgroups: 1.55 at
+// depth 4, the deepest that fits).  The blocked sweep takes 0.97 us a step on
+// the smallest grids (a launch per 8 steps), 1.3 at 512^2 and 3.0 at 1024^2, so
+// the resident one is chosen wherever it fits.
 static int res_auto_depth(const tdp_op *op, int variant)
 {
     const bool f64 = op->prec == TDP_F64;
@@ -576,8 +585,9 @@ static int res_auto_depth(const tdp_op *op, int variant)
     for (int k = 8; k >= 2; k -= 2) {
         if (!res_applies(op, k, 1)) continue;
         const int parts = variant && res_applies(op, k, 2) ? 2 : 1;
-        const int nt = res_tiles(op->n[0], op->n[1], k, f64, nullptr, nullptr);
-        double us = nt * parts <= op->ncu ? 2.5 / k + 0.6 : 3.0 / k + 0.85;
+        const int shape = res_shape(op, k, parts);
+        const int nt = res_tiles(op->n[0], op->n[1], k, f64, shape, nullptr, nullptr);
+        double us = shape == 2 ? 1.4 / k + 0.5 : (nt * parts <= op->ncu ? 1.35 / k + 0.7 : 3.0 / k + 0.85);
         if (variant) us *= 3 - parts;
         if (!best || us < best_us) {
             best = k;
@@ -815,7 +825,12 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
     a.nx = op->n[1];
     a.sc = op->sc;
     a.k = k;
-    const int nt = res_tiles(a.ny, a.nx, k, f64, &a.tiles_x, &a.tiles_y);
+    // passes: Table 1's field; Definition 4's two parts together or in turn
+    const int together = variant && Ns <= TDP_RES_MAXSTEPS && res_applies(op, k, 2) ? 2 : 1;
+    a.parts = together;
+    a.shape = res_shape(op, k, together);
+    a.ncu = op->ncu;
+    const int nt = res_tiles(a.ny, a.nx, k, f64, a.shape, &a.tiles_x, &a.tiles_y);
     a.m = f64 ? (const void *)op->m : (const void *)op->m32;
     a.dn = f64 ? (const void *)op->dn : (const void *)op->dn32;
     a.F = F;
@@ -824,8 +839,6 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
     a.poll_limit = op->res_force_abort ? 16 : (1 << 21);
     a.wait_bias = op->res_force_abort ? 1 : 0;
     const bool single = nt == 1;           // no exchange, nothing to wait for
-    // passes: Table 1's field; Definition 4's two parts together or in turn
-    const int together = variant && Ns <= TDP_RES_MAXSTEPS && res_applies(op, k, 2) ? 2 : 1;
     ResGate &gate = g_res_gate[op->device & 63];
     std::unique_lock<std::mutex> lock(gate.mu, std::defer_lock);
     if (!single) {
@@ -836,7 +849,6 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
     bool first = true;
     for (int p0 = 0; p0 < (variant ? 2 : 1); p0 += together) {
         const double *tab[2] = {nullptr, nullptr};
-        a.parts = together;
         for (int q = 0; q < together; ++q) {
             auto it = op->dtables.find(std::make_tuple(T, rho, p0 + q ? 2 : 0));
             if (it == op->dtables.end()) TDP_FAIL(TDP_EINVAL, "resident sweep: forcing table not staged");
@@ -857,7 +869,7 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
             a.out_step[0] = (jsnap > j0 && jsnap <= j0 + n) ? (int)(jsnap - j0) : 0;
             a.out_step[1] = last ? n : 0;
             if (!single)
-                TDP_CHECK_HIP(launch_res_init(op->res_slots, res_slot_bytes(f64, k) * nt * together,
+                TDP_CHECK_HIP(launch_res_init(op->res_slots, res_slot_bytes(f64, k, a.shape) * nt * together,
                                               op->res_abort, first, f64, s));
             first = false;
             if (f64)
@@ -907,7 +919,9 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
 static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
 {
     const bool f64 = op->prec == TDP_F64;
-    const int nt = res_tiles(op->n[0], op->n[1], k, f64, nullptr, nullptr);
+    const int parts = variant && (int64_t)T * op->nP <= TDP_RES_MAXSTEPS && res_applies(op, k, 2) ? 2 : 1;
+    const int shape = res_shape(op, k, parts);
+    const int nt = res_tiles(op->n[0], op->n[1], k, f64, shape, nullptr, nullptr);
     if (!op->res_abort &&
         (hipMalloc(&op->res_abort, sizeof(int)) != hipSuccess ||
          hipHostMalloc(&op->res_host, 2 * sizeof(int)) != hipSuccess))
@@ -918,8 +932,7 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
         op->res_id = ++g_res_ids;
     }
     if (nt > 1) {
-        const int parts = variant && res_applies(op, k, 2) ? 2 : 1;
-        const size_t n = res_slot_bytes(f64, k) * (size_t)nt * parts;
+        const size_t n = res_slot_bytes(f64, k, shape) * (size_t)nt * parts;
         if (n > op->res_slots_bytes) {
             TDP_CHECK_HIP(hipStreamSynchronize(op->stream));
             (void)hipFree(op->res_slots);

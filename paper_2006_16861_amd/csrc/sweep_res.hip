@@ -236,7 +236,7 @@ __device__ __forceinline__ void res_step(const T *__restrict__ cur, T *__restric
                                          const Rows<T, SC, R> &co, const T (&a)[R], T (&b)[R],
                                          T fas, T fbs)
 {
-    static_assert(R % 2 == 0 && R >= 8, "rows go in pairs");
+    static_assert(R % 2 == 0 && R >= 6, "rows go in pairs");
     constexpr int NP = R / 2;
     auto f0 = fl[2 * kResX], f1 = fl[3 * kResX];
     const Row3<T> south = row_at(cur + rs), north = row_at(cur + rn);
@@ -702,8 +702,15 @@ __global__ __launch_bounds__(1024) void k_res_recover(ResRecover a, Stencil<T> s
 }  // namespace
 
 // tile shapes: rows per lane x waves (64 columns), FP64 / FP32
-//   0: 12 x 4 / 16 x 4, two workgroups per compute unit
-//   1:  8 x 8 / 8 x 8, for grids of one tile
+//   0: 12 x 4 / 16 x 4, two workgroups per compute unit; where there is one (and
+//      k is at most the rows of a wave), 6 x 8 / 8 x 8 on the same rows: two
+//      waves per SIMD hide each other's latency.  512 x 512, k = 6: 0.945
+//      against 1.14 us a step in FP64, 0.818 against 0.93 in FP32
+//   1:  8 x 8 / 8 x 8, for grids of one tile (up to 48 rows in FP64: 6 x 8)
+//   2:  8 x 4 / 8 x 4, 32 rows, for grids of at most one such tile per compute
+//      unit: a step takes as long as a compute unit's rows are many.  300 x 300,
+//      k = 8: 0.745 against 1.01 us a step in FP64 (on 48 rows; k = 6 and 6 x 8
+//      waves: 0.94), 0.604 against 0.75 in FP32; the blocked sweep 0.99 and 1.7
 template <typename T>
 struct ResShape0;
 template <>
@@ -717,24 +724,25 @@ struct ResShape0<float> {
 
 int res_tile_rows(bool f64, int shape)
 {
+    if (shape == 2) return 32;
     return shape == 1 ? 64 : (f64 ? ResShape0<double>::R * ResShape0<double>::W
                                   : ResShape0<float>::R * ResShape0<float>::W);
 }
 
-size_t res_slot_bytes(bool f64, int k)
+size_t res_slot_bytes(bool f64, int k, int shape)
 {
-    return 3 * 2 * (size_t)res_band(res_tile_rows(f64, 0), k) * (f64 ? sizeof(double) : sizeof(float));
+    return 3 * 2 * (size_t)res_band(res_tile_rows(f64, shape), k) * (f64 ? sizeof(double) : sizeof(float));
 }
 
-int res_tiles(int ny, int nx, int k, bool f64, int *tiles_x, int *tiles_y)
+int res_tiles(int ny, int nx, int k, bool f64, int shape, int *tiles_x, int *tiles_y)
 {
     if (k < 2 || k > 8 || (k & 1)) return 0;
-    if (ny <= res_tile_rows(f64, 1) && nx <= kResX) {      // one tile of either shape
+    if (ny <= res_tile_rows(f64, 1) && nx <= kResX) {      // one tile
         if (tiles_x) *tiles_x = 1;
         if (tiles_y) *tiles_y = 1;
         return 1;
     }
-    const int rows = res_tile_rows(f64, 0), ox = kResX - 2 * k, oy = rows - 2 * k;
+    const int rows = res_tile_rows(f64, shape), ox = kResX - 2 * k, oy = rows - 2 * k;
     // tile t covers 64 + t ox columns with the ones before it
     const int tx = nx <= kResX ? 1 : 1 + (nx - kResX + ox - 1) / ox;
     const int tyc = ny <= rows ? 1 : 1 + (ny - rows + oy - 1) / oy;
@@ -777,23 +785,34 @@ int res_workgroups_per_cu(int k, int sc, bool f64)
 template <typename T, int SC>
 static hipError_t launch_res_sc(const ResArgs &a, const Stencil<T> &st, hipStream_t s)
 {
-    constexpr int R = ResShape0<T>::R, W = ResShape0<T>::W;
+    constexpr int R = ResShape0<T>::R, W = ResShape0<T>::W, RH = R / 2, WH = 2 * W;
     const int nt = a.tiles_x * a.tiles_y * a.parts;
+#define TDP_RES(R, W, K, MULTI) \
+    hipLaunchKernelGGL((k_sweep2d_res<T, SC, R, W, K, MULTI>), dim3(nt), dim3(64 * W), 0, s, a, st)
     if (a.tiles_x * a.tiles_y == 1) {
-        // one tile: 8 waves of 8 rows where 4 waves are not enough rows
-        if (a.ny <= R * W)
-            hipLaunchKernelGGL((k_sweep2d_res<T, SC, R, W, 8, false>), dim3(nt), dim3(64 * W), 0, s, a, st);
-        else
-            hipLaunchKernelGGL((k_sweep2d_res<T, SC, 8, 8, 8, false>), dim3(nt), dim3(512), 0, s, a, st);
-        return hipGetLastError();
-    }
-#define TDP_RES(K) \
-    hipLaunchKernelGGL((k_sweep2d_res<T, SC, R, W, K, true>), dim3(nt), dim3(64 * W), 0, s, a, st)
-    switch (a.k) {
-    case 2: TDP_RES(2); break;
-    case 4: TDP_RES(4); break;
-    case 6: TDP_RES(6); break;
-    default: TDP_RES(8); break;
+        if (a.ny <= R * W) TDP_RES(RH, WH, 2, false);
+        else TDP_RES(8, 8, 2, false);
+    } else if (a.shape == 2) {
+        switch (a.k) {
+        case 2: TDP_RES(8, 4, 2, true); break;
+        case 4: TDP_RES(8, 4, 4, true); break;
+        case 6: TDP_RES(8, 4, 6, true); break;
+        default: TDP_RES(8, 4, 8, true); break;
+        }
+    } else if (nt <= a.ncu && a.k <= RH) {
+        switch (a.k) {
+        case 2: TDP_RES(RH, WH, 2, true); break;
+        case 4: TDP_RES(RH, WH, 4, true); break;
+        case 6: TDP_RES(RH, WH, 6, true); break;
+        default: if constexpr (RH >= 8) TDP_RES(RH, WH, 8, true);
+        }
+    } else {
+        switch (a.k) {
+        case 2: TDP_RES(R, W, 2, true); break;
+        case 4: TDP_RES(R, W, 4, true); break;
+        case 6: TDP_RES(R, W, 6, true); break;
+        default: TDP_RES(R, W, 8, true); break;
+        }
     }
 #undef TDP_RES
     return hipGetLastError();

@@ -198,6 +198,8 @@ struct ResArgs {
     int ny, nx;
     int sc;
     int k;                      // steps between exchanges: 2, 4, 6 or 8
+    int shape;                  // tile shape: 0, or 2 (workgroups <= compute units)
+    int ncu;                    // compute units
     int nsteps;                 // steps of this launch, 1..TDP_RES_MAXSTEPS
     int tiles_x, tiles_y;
     int parts;                  // real fields advanced side by side (1, or 2: Definition 4)
@@ -234,10 +236,10 @@ struct ResRecover {
 hipError_t launch_res_recover(const ResRecover &a, const Stencil<double> &st,
                               const Stencil<float> &st32, bool f64, hipStream_t s);
 int res_tile_rows(bool f64, int shape);
-size_t res_slot_bytes(bool f64, int k);   // exchange-buffer bytes per workgroup
+size_t res_slot_bytes(bool f64, int k, int shape);   // exchange-buffer bytes per workgroup
 int res_workgroups_per_cu(int k, int sc, bool f64);   // queried once; call before any capture
-// tiles of the resident grid at exchange depth k (0 if k is not supported)
-int res_tiles(int ny, int nx, int k, bool f64, int *tiles_x, int *tiles_y);
+// tiles of the resident grid at exchange depth k (0 if k is not supported) and tile shape
+int res_tiles(int ny, int nx, int k, bool f64, int shape, int *tiles_x, int *tiles_y);
 
 // 3-D sweep streamed along axis 0 (sweep3d.hip), one step per launch.
 // shape 0/1/2: 8 x 64 (4 waves x 2 rows), 16 x 64 (4 waves x 4 rows), 16 x 64

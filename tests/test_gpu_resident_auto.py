@@ -55,6 +55,30 @@ def test_default_sweep_matches_oracle(n):
         g32.set_tuning()
 
 
+@pytest.mark.parametrize("n", [(33, 130), (430, 430), (450, 470), (512, 512), (560, 600), (700, 640)])
+def test_tile_shapes(n):
+    """Every exchange depth where the tile shape changes with the grid: 32-row
+    tiles (430 x 430: the last that fit at depth 8), one 48- or 64-row tile per
+    compute unit, two.  FP64 against the blocked sweep at 1e-13, the bar of the
+    other kernel against kernel comparisons; FP32 equal to it."""
+    from paper_2006_16861_amd import tdp
+    p = inputs.random_medium(n, seed=67, width=4)
+    print(f"[case] tile shapes {n}", file=sys.stderr, flush=True)
+    for prec in (tdp.F64, tdp.F32):
+        g = tdp.operator_from_problem(p, prec=prec)
+        for variant in (0, 1):
+            g.set_tuning(kernel=2, tb_depth=4, tile=5)
+            U = host(g.precond(dev(p.F), 2, 0.25, variant=variant))
+            for k in (2, 4, 6, 8):
+                g.set_tuning(kernel=5, tb_depth=k)
+                V = host(g.precond(dev(p.F), 2, 0.25, variant=variant))
+                if prec == tdp.F32:
+                    assert np.array_equal(U, V), (variant, k)
+                else:
+                    assert rel(V, U) <= 1e-13, (variant, k)
+        assert g.resident_aborts == 0
+
+
 @pytest.mark.parametrize("n,variant", [((60, 50), 0), ((60, 130), 0), ((60, 130), 1)])
 def test_runs_longer_than_one_launch(n, variant):
     """N_s = 4104 steps: two launches (4096 + 8)."""
