@@ -270,7 +270,9 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *  kernel       0 auto (kernel, depth and tile chosen by the library: in 2-D
  *               with node damping and no corner mass entries the resident
  *               tiles (kernel 5) where the grid's tiles fit the device, at the
- *               exchange depth of least cost, else the
+ *               exchange depth of least cost, on larger
+ *               ones (13 * 2^17 nodes up) the streamed 2-D sweep, 8 steps per
+ *               launch, which has no number here, else the
  *               blocked 2-D sweep on tile 5 (FP64) or 8 (FP32) at depth 8, with
  *               the cell damping on tile 7 (FP64) or 4 (FP32); in 3-D the
  *               two-step streamed sweep for tables without corner entries
@@ -344,7 +346,7 @@ int tdp_op_force_resident_abort(tdp_op *op, int on);
 /* Autotuner: times each sweep variant applicable to this op (one step per
  * launch; blocked tile shapes x depths 2-10, 12, 16 (4 x depth
  * at most the tile's rows) and the resident tiles at exchange depths 2, 4, 6,
- * 8 for the 2-D Table 1 loop; the blocked I_abd tiles
+ * 8 for the 2-D Table 1 loop, and kernel 0 where it streams; the blocked I_abd tiles
  * x depths 2, 3, 4, 6, 8 with the 2-D cell damping; in 3-D the one-step
  * streamed shapes x chunk lengths 4, 8, 16, 32, 64 and the two-step shapes x
  * shortest runs 2, 8 and 32) over

@@ -545,7 +545,8 @@ static int ensure_complex_fields(tdp_op *op)
 // the blocked 2-D kernel (k steps per launch), 3 / 4 the streamed 3-D kernels
 // (depth = planes per chunk), 5 the resident-tile 2-D sweep (depth = steps
 // between exchanges).  kernel 0 chooses all three: in 2-D the resident sweep
-// where it applies, else the blocked one on the 32 x 64 tile (FP64) or the
+// where it applies, the streamed one (reported as kernel 6) on large grids,
+// else the blocked one on the 32 x 64 tile (FP64) or the
 // 128 x 64 tile (FP32) at depth 8; in 3-D the two-step streamed sweep, or
 // the one-step one on 8 x 64 columns with the chunk below.
 // Kernel 5 applies to node damping and tables without corner mass terms, on
@@ -624,6 +625,17 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             kern = 2;
             k = 8;
             t = f64 ? 5 : 8;
+            // Streamed (internal: kernel 6) where the grid gives its strips
+            // runs that are long against the rows they start with: us per
+            // step, blocked and streamed, FP64 4.4 and 5.2 at 1150^2, 5.6
+            // and 5.5 at 1300^2, 8.0 and 6.3 at 1500 x 1600; FP32 4.6 and 4.35 at
+            // 1500^2
+            if (op->dform == TDP_DAMP_NODE && op->mc <= 2 && op->N >= (13 << 17)) {
+                *kernel = 6;
+                *depth = sweep2d_stream_depth();
+                *tile = t;
+                return;
+            }
         } else if (op->sc <= 3 && op->mc <= 2) {
             // 3-D tables without corner entries: two steps per launch with
             // the rows in registers.  FP32 on tiles of 16 rows below about
@@ -699,9 +711,12 @@ static int ensure_tb_fields(tdp_op *op)
 // (u0, u1) and (v0, v1).
 // Real-field loops (Table 1's recurrence with the forcing table `tabv`): the
 // final field goes to out_final and, when out_snap is given, the sample
-// u_{N_s - q} to out_snap (stride-2 doubles inside a complex128 array).
+// u_{N_s - q} to out_snap (stride-2 doubles inside a complex128 array).  With
+// `streamed`, launches of exactly `depth` steps are the streamed form's; a
+// remainder of fewer steps takes the blocked tile.
 static int issue_steps_tb(tdp_op *op, const LoopBufs &lb, int T, double rho, int depth, int tile,
-                          const void *Fin, int tabv, double *out_final, double *out_snap)
+                          bool streamed, const void *Fin, int tabv, double *out_final,
+                          double *out_snap)
 {
     hipStream_t s = op->stream;
     const ForcingSrc tab = forcing_src(op, T, rho, tabv, lb);
@@ -719,8 +734,9 @@ static int issue_steps_tb(tdp_op *op, const LoopBufs &lb, int T, double rho, int
     a.m = op->prec == TDP_F64 ? (const void *)op->m : (const void *)op->m32;
     a.dn = op->prec == TDP_F64 ? (const void *)op->dn : (const void *)op->dn32;
     a.F = Fin;
-    for (int64_t j0 = 0; j0 < Ns; j0 += depth) {
-        const int k = (int)std::min<int64_t>(depth, Ns - j0);
+    for (int64_t j0 = 0; j0 < Ns;) {
+        const bool st = streamed && Ns - j0 >= depth;
+        const int k = (int)std::min<int64_t>(streamed && !st ? std::min(depth, 8) : depth, Ns - j0);
         a.u_in = cur;
         a.up_in = prev;
         a.u_out = ncur;
@@ -735,10 +751,14 @@ static int issue_steps_tb(tdp_op *op, const LoopBufs &lb, int T, double rho, int
         a.cf.out[0] = out_snap;
         a.cf.out_step[1] = (Ns > j0 && Ns <= j0 + k) ? (int)(Ns - j0) : 0;
         a.cf.out[1] = out_final;
-        if (op->prec == TDP_F64)
+        if (st)
+            TDP_CHECK_HIP(op->prec == TDP_F64 ? launch_sweep2d_stream_f64(a, op->st_step, op->ncu, s)
+                                              : launch_sweep2d_stream_f32(a, op->st_step32, op->ncu, s));
+        else if (op->prec == TDP_F64)
             TDP_CHECK_HIP(launch_sweep2d_tb_f64(a, op->st_step, s));
         else
             TDP_CHECK_HIP(launch_sweep2d_tb_f32(a, op->st_step32, s));
+        j0 += k;
         std::swap(cur, ncur);
         std::swap(prev, nprev);
     }
@@ -1098,7 +1118,8 @@ static int issue_steps_loop(tdp_op *op, const LoopBufs &lb, int T, double rho, i
     sweep_plan(op, variant, &kern, &depth, &tile, false);
     double *Ud = (double *)U;
     auto real_pass = [&](int tabv, double *fin, double *snap) -> int {
-        if (kern == 2) return issue_steps_tb(op, lb, T, rho, depth, tile, Fin, tabv, fin, snap);
+        if (kern == 2 || kern == 6)
+            return issue_steps_tb(op, lb, T, rho, depth, tile, kern == 6, Fin, tabv, fin, snap);
         if (kern == 4) return issue_steps_3d2(op, lb, T, rho, depth, tile, Fin, tabv, fin, snap);
         return issue_steps_real1(op, lb, T, rho, kern, depth, tile, Fin, tabv, fin, snap);
     };
@@ -1214,9 +1235,10 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
             TDP_CHECK(issue_steps_res(op, T, rho, depth, F, variant, U, recover));
             return recover ? TDP_OK : res_finish(op, T, rho, variant, F, U, direct, pending);
         }
-        if (kern == 2 || kern == 4) TDP_CHECK(ensure_tb_fields(op));
+        if (kern == 2 || kern == 4 || kern == 6) TDP_CHECK(ensure_tb_fields(op));
+        if (kern == 6) sweep2d_stream_prepare(op->prec == TDP_F64, op->sc);
         if (kern == 4) sweep3d_stream2_prepare(op->prec == TDP_F64, tile);
-        launches = kern == 2 ? (Ns + depth - 1) / depth
+        launches = kern == 2 || kern == 6 ? (Ns + depth - 1) / depth + 1
                  : kern == 4 ? (Ns + 1) / 2
                              : Ns;
         // two real passes (one launch for both with the blocked I_abd kernel)
@@ -1382,6 +1404,15 @@ extern "C" int tdp_op_autotune(tdp_op *op, int periods_T, double rho, int varian
             for (int k : depths)
                 if (4 * k <= rows && 4 * k <= tb2d_tile_cols(tile)) cand.push_back({2, k, 1, tile});
         }
+    }
+    // the streamed sweep is reached through the automatic choice only
+    if (op->ndim == 2 && op->dform == TDP_DAMP_NODE) {
+        const tdp_tuning was = op->tune;
+        int kern, depth, tile;
+        op->tune = {0, 0, 1, 0};
+        sweep_plan(op, variant, &kern, &depth, &tile);
+        op->tune = was;
+        if (kern == 6) cand.push_back({0, 0, 1, 0});
     }
     for (int k : {2, 4, 6, 8})
         if (res_applies(op, k, 1)) cand.push_back({5, k, 1, 0});
