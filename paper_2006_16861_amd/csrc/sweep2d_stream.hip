@@ -24,11 +24,12 @@
 // stores of what is not the wave's own are dropped the same way.
 //
 // us per step, the blocked sweep (32 x 64 tiles in FP64, 128 x 64 in FP32, depth
-// 8) and this one: FP64 23.6 and 16.7 at 2999 x 2503, 12.5 and 8.4 at 2000 x
-// 2000, 5.6 and 5.4 at 1300 x 1300; FP32 13.2 and 9.5, 7.1 and 6.0, 4.6 and 4.35 at
-// 1500 x 1500.  At 2999 x 2503 it is held by HBM: 64 bytes a node and launch are
-// 3.6 TB/s, and the columns and rows that strips and runs share, read again
-// in part, bring the traffic to 4 to 5.
+// 8) and this one: FP64 23.6 and 15.8 at 2999 x 2503, 12.5 and 8.4 to 9.2 at 2000
+// x 2000, 7.9 and 6.8 at 1500 x 1600; FP32 13.2 and 9.5, 7.1 and 6.0, 4.6 and 4.35
+// at 1500 x 1500.  At 2999 x 2503 it is held by HBM: a launch moves 561 MB (436
+// read, 125 written; it cannot do with less than 480) at 4.4 TB/s.  Smaller
+// grids are held by the length of a run against the 14 rows it forms beside
+// its own, and by latency with two waves per SIMD.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -182,7 +183,7 @@ struct Ring<float, SC, K> {
     __device__ __forceinline__ float before(int, bool) const { return 0.0f; }
 };
 
-template <typename T, int SC, int K, int OCC, bool OUT>
+template <typename T, int SC, int K, int OCC, bool NTS, bool OUT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC)))
 void k_sweep2d_stream(const T *__restrict__ u, const T *__restrict__ um, T *__restrict__ uo,
                       T *__restrict__ upo, const T *__restrict__ m, const T *__restrict__ dn,
@@ -192,6 +193,10 @@ void k_sweep2d_stream(const T *__restrict__ u, const T *__restrict__ um, T *__re
     using V2 = typename V2t<T>::type;
     constexpr int OX = 64 - 2 * K;
     constexpr bool KEEP = sizeof(T) == 4;      // C's x-neighbours too, where registers allow
+    // u_{j-1}, d and F are read once: non-temporal where the launch's working
+    // set exceeds the 256 MB MALL (2999 x 2503 FP64: 15.8 against 16.7 us a step;
+    // in FP32, where it fits, 10.1 against 9.6)
+    constexpr int NT = NTS ? 2 : 0;
     // F and, in FP64, d of the rows in flight
     constexpr int KD = sizeof(T) == 8 ? K : 1;
     __shared__ V2 fl[K][64];
@@ -223,9 +228,9 @@ void k_sweep2d_stream(const T *__restrict__ u, const T *__restrict__ um, T *__re
         bload<0>(p.u, rsrc_of(u + r0, in0 ? rbytes : 0), lane * (unsigned)sizeof(T));
         bload<0>(p.c, rsrc_of(m + r0 + a, (unsigned)a <= (unsigned)ny && a < aend ? cbytes : 0),
                  lane * (unsigned)sizeof(T));
-        bload<0>(p.um, rsrc_of(um + r1, in1 ? rbytes : 0), lane * (unsigned)sizeof(T));
-        bload<0>(p.d, rsrc_of(dn + r1, in1 ? rbytes : 0), lane * (unsigned)sizeof(T));
-        bload<0>(p.f, rsrc_of(F + r1, in1 ? 2 * rbytes : 0), lane * (unsigned)sizeof(V2));
+        bload<NT>(p.um, rsrc_of(um + r1, in1 ? rbytes : 0), lane * (unsigned)sizeof(T));
+        bload<NT>(p.d, rsrc_of(dn + r1, in1 ? rbytes : 0), lane * (unsigned)sizeof(T));
+        bload<NT>(p.f, rsrc_of(F + r1, in1 ? 2 * rbytes : 0), lane * (unsigned)sizeof(V2));
     };
 
     Ring<T, SC, K> co;
@@ -336,7 +341,7 @@ int stream_per_cu()
 {
     static const int v = [] {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep2d_stream<T, SC, K, OCC, false>, 64,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep2d_stream<T, SC, K, OCC, true, false>, 64,
                                                          0) != hipSuccess || nb < 1)
             nb = 1;
         return nb;
@@ -364,13 +369,19 @@ hipError_t launch_stream(const TBArgs &a, const Stencil<T> &st, int ncu, hipStre
     }
     const int nrun = (a.ny + len - 1) / len;
     const int per_xcd = (strips * nrun + 7) / 8;
-#define TDP_STREAM(OUT)                                                                                 \
-    hipLaunchKernelGGL((k_sweep2d_stream<T, SC, K, OCC, OUT>), dim3(8 * per_xcd), dim3(64), 0, s,       \
+#define TDP_STREAM(NTS, OUT)                                                                                 \
+    hipLaunchKernelGGL((k_sweep2d_stream<T, SC, K, OCC, NTS, OUT>), dim3(8 * per_xcd), dim3(64), 0, s,       \
                        (const T *)a.u_in, (const T *)a.up_in, (T *)a.u_out, (T *)a.up_out,              \
                        (const T *)a.m, (const T *)a.dn, (const typename V2t<T>::type *)a.F, a.ny, a.nx, \
                        st, a.cf, strips, nrun, len, per_xcd)
-    if (a.cf.out_step[0] || a.cf.out_step[1]) TDP_STREAM(true);
-    else TDP_STREAM(false);
+    const bool out = a.cf.out_step[0] || a.cf.out_step[1];
+    if ((int64_t)8 * sizeof(T) * a.ny * a.nx > ((int64_t)256 << 20)) {
+        if (out) TDP_STREAM(true, true);
+        else TDP_STREAM(true, false);
+    } else {
+        if (out) TDP_STREAM(false, true);
+        else TDP_STREAM(false, false);
+    }
 #undef TDP_STREAM
     return hipGetLastError();
 }
