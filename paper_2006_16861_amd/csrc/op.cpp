@@ -1236,7 +1236,6 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
             return recover ? TDP_OK : res_finish(op, T, rho, variant, F, U, direct, pending);
         }
         if (kern == 2 || kern == 4 || kern == 6) TDP_CHECK(ensure_tb_fields(op));
-        if (kern == 6) sweep2d_stream_prepare(op->prec == TDP_F64, op->sc);
         if (kern == 4) sweep3d_stream2_prepare(op->prec == TDP_F64, tile);
         launches = kern == 2 || kern == 6 ? (Ns + depth - 1) / depth + 1
                  : kern == 4 ? (Ns + 1) / 2

@@ -337,24 +337,11 @@ void k_sweep2d_stream(const T *__restrict__ u, const T *__restrict__ um, T *__re
 }
 
 template <typename T, int SC, int K, int OCC>
-int stream_per_cu()
-{
-    static const int v = [] {
-        int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sweep2d_stream<T, SC, K, OCC, true, false>, 64,
-                                                         0) != hipSuccess || nb < 1)
-            nb = 1;
-        return nb;
-    }();
-    return v;
-}
-
-template <typename T, int SC, int K, int OCC>
 hipError_t launch_stream(const TBArgs &a, const Stencil<T> &st, int ncu, hipStream_t s)
 {
     constexpr int OX = 64 - 2 * K;
     const int strips = a.nx <= 63 ? 1 : 1 + (a.nx - 63 + OX - 1) / OX;
-    const int64_t slots = (int64_t)ncu * stream_per_cu<T, SC, K, OCC>();
+    const int64_t slots = (int64_t)ncu * 4 * OCC;        // resident waves
     // runs of K t + 2 rows take K (t + 2) iterations, whole turns of the loop
     int len = 2;
     double best = INFINITY;
@@ -388,16 +375,6 @@ hipError_t launch_stream(const TBArgs &a, const Stencil<T> &st, int ncu, hipStre
 
 }  // namespace
 
-void sweep2d_stream_prepare(bool f64, int sc)
-{
-    if (f64) {
-        if (sc > 2) stream_per_cu<double, 3, kSteps, kWaves>();
-        else stream_per_cu<double, 2, kSteps, kWaves>();
-    } else {
-        if (sc > 2) stream_per_cu<float, 3, kSteps, kWaves>();
-        else stream_per_cu<float, 2, kSteps, kWaves>();
-    }
-}
 int sweep2d_stream_depth() { return kSteps; }
 hipError_t launch_sweep2d_stream_f64(const TBArgs &a, const Stencil<double> &st, int ncu, hipStream_t s)
 {

@@ -26,13 +26,11 @@
 // It took the place of a form that read every stencil point of both steps
 // from LDS (about 47 words per node and plane) and spent 2.3 to 3 us on a plane
 // whatever the grid.  Per step, that form and this one: FP64 14.1 and 6.7 us at
-// 64^3, 20.7 and 17.4 at 128^3, 146 and 118 at 256^3 (4.5 TB/s of the 32 bytes
-// a node and step); FP32 11.4 and 5.2, 16.0 and 12.0, 96 and 72.  At 256^3 it is
-// held by HBM in FP64 and in FP32 by the loads in flight: the SIMDs issue 57%
-// of the time, 38% vector arithmetic, with the two waves each (FP64, and the
-// FP32 form with four rows) that 212 registers leave.  Two nodes per lane
-// (half a wave to a row, 16-byte loads) halve the memory instructions and
-// measured the same: 125.8 and 72.5.
+// 64^3, 20.7 and 17.4 at 128^3, 146 and 118 at 256^3; FP32 11.4 and 5.2, 16.0 and
+// 12.0, 96 and 72 (short applications; in long ones 107 and 61 at 256^3).  There
+// it is held by HBM: 1250 MB a launch at 5.8 TB/s in FP64, 689 MB at 5.6 in FP32.
+// Two nodes per lane (half a wave to a row, 16-byte loads) halve the memory
+// instructions and measured the same: 125.8 and 72.5 us.
 //
 // A tile is 64 columns x EY = R W rows (columns x0 .. x0+63, x0 = ox bx; rows
 // y0 .. y0+EY-1, y0 = (EY-2) by).  Each level costs a column on either side,

@@ -133,7 +133,6 @@ struct TBArgs {
 // The streamed form (sweep2d_stream.hip): exactly sweep2d_stream_depth steps per
 // launch, tables without corner mass entries; `shape` is not used.
 int sweep2d_stream_depth();
-void sweep2d_stream_prepare(bool f64, int sc);   // call before any stream capture
 hipError_t launch_sweep2d_stream_f64(const TBArgs &a, const Stencil<double> &st, int ncu, hipStream_t s);
 hipError_t launch_sweep2d_stream_f32(const TBArgs &a, const Stencil<float> &st, int ncu, hipStream_t s);
 
