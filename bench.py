@@ -336,7 +336,7 @@ def form_precision(rho):
         tname = 'double' if word == 8 else 'float'
         kname = (f"k_sweep3d_stream<{tname}> shape={tun['tile']} z-chunk={tun['tb_depth']}"
                  if tun["kernel"] == 3 else
-                 f"k_sweep3d_stream2<{tname}> shape={tun['tile']} (two steps per launch)"
+                 f"k_sweep3d_reg2<{tname}> tile={tun['tile']} (two steps per launch)"
                  if tun["kernel"] == 4 else f"kernel {tun['kernel']}")
         spl = {4: 2}.get(tun["kernel"], 1)
         words_launch = WORDS_PER_NODE_LAUNCH if spl > 1 else WORDS_PER_NODE_STEP
@@ -947,7 +947,8 @@ def main():
     elif tun["kernel"] == 3:
         kname = f"k_sweep3d_stream<{tname}> shape={tun['tile']} z-chunk={tun['tb_depth']}"
     elif tun["kernel"] == 4:
-        kname = f"k_sweep3d_stream2<{tname}> shape={tun['tile']} z-chunk={tun['tb_depth']} (2 steps)"
+        form = "stream2" if args.scheme == "q1" else "reg2"
+        kname = f"k_sweep3d_{form}<{tname}> tile={tun['tile']} shortest run={tun['tb_depth']} (2 steps)"
     else:
         kname = f"k_sweep<{tname}> (one step per launch)"
     # the counters were taken with the compact scheme
