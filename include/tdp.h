@@ -274,10 +274,14 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               ones (13 * 2^17 nodes up) the streamed 2-D sweep, 8 steps per
  *               launch, which has no number here, else the
  *               blocked 2-D sweep on tile 5 (FP64) or 8 (FP32) at depth 8, with
- *               the cell damping on tile 7 (FP64) or 4 (FP32); in 3-D the
+ *               the cell damping on tile 7 (FP64, and FP32 below 3 * 2^16
+ *               nodes), 4 or (FP32 from 3 * 2^19) 5, from 3 * 2^19 nodes at depth
+ *               6; in 3-D the
  *               two-step streamed sweep for tables without corner entries
  *               (FP64 tile 1; FP32 tile 2, tile 0 below 3 * 2^20 nodes) and
- *               the one-step streamed sweep on tile 0 otherwise; tb_depth and
+ *               for the others kernel 1 below 3 * 2^17 nodes (Table 1 form), then
+ *               kernel 4 on tile 0, in FP64 kernel 3 on tile 0 from 3 * 2^20
+ *               nodes; tb_depth and
  *               tile ignored),
  *               1 one step per launch, 2 temporally blocked (2-D; with the
  *               cell damping, tiles 5 and 7 in FP64 and 4..7 in FP32, mass

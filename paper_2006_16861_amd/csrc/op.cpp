@@ -547,8 +547,8 @@ static int ensure_complex_fields(tdp_op *op)
 // between exchanges).  kernel 0 chooses all three: in 2-D the resident sweep
 // where it applies, the streamed one (reported as kernel 6) on large grids,
 // else the blocked one on the 32 x 64 tile (FP64) or the
-// 128 x 64 tile (FP32) at depth 8; in 3-D the two-step streamed sweep, or
-// the one-step one on 8 x 64 columns with the chunk below.
+// 128 x 64 tile (FP32) at depth 8; in 3-D the two-step sweep, or
+// (corner entries) the one-step ones by size.
 // Kernel 5 applies to node damping and tables without corner mass terms, on
 // grids whose tiles are resident all at once; elsewhere, and with resident =
 // false (the allocation-free entry point, a stream under capture), the plan
@@ -649,10 +649,31 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             k = 2;
             t = f64 ? 1 : (op->N < (3 << 20) ? 0 : 2);
         } else {
-            kern = 3;
-            k = t = 0;
+            // 3-D tables with corner entries (same results, bit for bit, on
+            // every kernel).  A small grid gives the streamed kernels too few
+            // columns and runs: one step per launch, one node per thread (Def. 4
+            // has only its complex form there and takes the next); then two
+            // steps per launch; in FP64 one again from about 3 * 2^20 nodes.
+            // us per step, kernels 1 / 4 / 3 (27 points): FP64 7.5 / 9.7 / 16.9
+            // at 64^3, 16.7 / 15.8 / 17.9 at 80^3, 42 / 32 / 37 at 131 x 150 x
+            // 117, 93 / 65 / 62 at 160^3; FP32 5.9 / 7.6 / 15.5 at 64^3, 12.3 /
+            // 12.1 / 17.6 at 100 x 90 x 110, 35 / 31.6 / 35 at 160^3, 112 / 81 / 87
+            // at 256 x 200 x 240
+            kern = variant == 0 && op->N < (3 << 17) ? 1 : (!f64 || op->N < (3 << 20) ? 4 : 3);
+            k = kern == 4 ? 2 : 0;
+            t = 0;
         }
-        if (op->dform == TDP_DAMP_CELL) t = f64 ? 7 : 4;
+        // I_abd tiles (same results on each): few rows where workgroups are few,
+        // less depth where HBM is near.  us per step: FP32 tiles 7 / 4 / 5 (at
+        // depth 6) 1.9 / 2.7 / 2.3 at 300^2, 2.9 / 2.7 / 2.9 at 500 x 600, 6.9 / 5.0
+        // / 5.35 at 1024^2, 11.7 / 8.8 / 7.7 at 1500 x 1300, 32 / 23 / 20 at 2400^2;
+        // FP64 tile 7 at depths 8 and 6: 5.6 and 6.3 at 800 x 700, 16.9 and 15.3
+        // at 1500 x 1300, 48.6 and 46.5 at 2400^2
+        if (op->dform == TDP_DAMP_CELL) {
+            const bool large = op->N >= (3 << 19);
+            t = f64 || op->N < (3 << 16) ? 7 : (large ? 5 : 4);
+            if (op->ndim == 2) k = large ? 6 : 8;
+        }
     }
     // I_abd: the blocked 2-D kernel on the tiles that hold its per-node state
     // (mass tables without corner entries), else one step per launch
