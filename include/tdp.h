@@ -304,8 +304,10 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               way it is counted in tdp_op_info.res_aborts and the op's
  *               automatic choice leaves this kernel out from then on, until
  *               tdp_op_set_tuning.  Where kernel 5 does not apply it falls back
- *               to the auto choice; a stream under capture takes the blocked
- *               sweep); inapplicable choices fall back to 1
+ *               to the auto choice; a call that the caller captures into a
+ *               graph (use_graph = 0, after one eager call of the same form)
+ *               takes the blocked or the streamed sweep); inapplicable choices
+ *               fall back to 1
  *  tb_depth     kernel 2: steps per launch, 1..16 (0 auto);
  *               kernel 5: steps between halo exchanges, 2, 4, 6 or 8 (0: 4);
  *               kernel 3: planes per chunk (0 auto: 32, halved down

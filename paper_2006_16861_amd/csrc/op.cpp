@@ -956,7 +956,8 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
 
 // Buffers of the resident sweep: exchange slots of every tile, the abort word,
 // its pinned mirror, device copies of the forcing tables the loop reads, and
-// the field pairs that hand over between launches.
+// the field pairs that hand over between launches (and hold the fields of the
+// blocked sweep if the caller captures a later call: see precond_impl).
 static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
 {
     const bool f64 = op->prec == TDP_F64;
@@ -999,7 +1000,7 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
         }
         op->dtables.emplace(key, d);
     }
-    return (int64_t)T * op->nP > TDP_RES_MAXSTEPS ? ensure_tb_fields(op) : TDP_OK;
+    return ensure_tb_fields(op);
 }
 
 // After a resident loop: the abort word is raised when a tile waited in vain
@@ -1237,9 +1238,10 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
         ++op->res_aborts;
         op->res_off = true;
     }
-    // a stream that is being captured by the caller takes the blocked sweep
-    // (the resident launches are ordered against each other by events that a
-    // capture cannot hold)
+    // a stream that is being captured by the caller (with use_graph = 0: a
+    // capture does not hold another) takes the blocked or streamed sweep, since
+    // the resident launches are ordered against each other by events that a
+    // capture cannot hold.  It may not allocate: an earlier call has
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (op->ndim == 2 && !op->own_stream) TDP_CHECK_HIP(hipStreamIsCapturing(op->stream, &cap));
     const bool resident = cap == hipStreamCaptureStatusNone;
