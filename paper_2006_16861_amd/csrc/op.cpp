@@ -847,6 +847,20 @@ struct ResGate {
 };
 ResGate g_res_gate[64];
 std::atomic<uint64_t> g_res_ids{0};
+
+// Records the gate's event when it goes out of scope: behind the last launch
+// of the application, its recovery included, and on every error exit too.
+struct ResGateRecord {
+    ResGate *gate = nullptr;
+    uint64_t id = 0;
+    hipStream_t s = nullptr;
+    ~ResGateRecord()
+    {
+        if (!gate) return;
+        if (hipEventRecord(gate->ev, s) == hipSuccess) gate->last = id;
+        else (void)hipStreamSynchronize(s);
+    }
+};
 }  // namespace
 
 // Resident-tile loop (kernel 5): launches of up to TDP_RES_MAXSTEPS steps over
@@ -882,10 +896,14 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
     const bool single = nt == 1;           // no exchange, nothing to wait for
     ResGate &gate = g_res_gate[op->device & 63];
     std::unique_lock<std::mutex> lock(gate.mu, std::defer_lock);
+    ResGateRecord record;                  // (destroyed before the lock)
     if (!single) {
         lock.lock();
         if (!gate.ev) TDP_CHECK_HIP(hipEventCreateWithFlags(&gate.ev, hipEventDisableTiming));
         if (gate.last && gate.last != op->res_id) TDP_CHECK_HIP(hipStreamWaitEvent(s, gate.ev, 0));
+        record.gate = &gate;
+        record.id = op->res_id;
+        record.s = s;
     }
     bool first = true;
     for (int p0 = 0; p0 < (variant ? 2 : 1); p0 += together) {
@@ -920,10 +938,6 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
             std::swap(cur, ncur);
             std::swap(prev, nprev);
         }
-    }
-    if (!single) {
-        TDP_CHECK_HIP(hipEventRecord(gate.ev, s));
-        gate.last = op->res_id;
     }
     if (!single && recover) {
         ResRecover r{};

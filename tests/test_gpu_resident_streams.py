@@ -59,3 +59,39 @@ def test_callers_capture_after_a_warm_up(prec, variant):
             want = ref.precond(F, 2, 0.25, variant=variant)
         s.synchronize()
         assert np.array_equal(host(out), host(want)), i
+
+
+def test_recovery_is_over_before_the_next_resident_run():
+    """A resident run whose tiles need the device for themselves starts only
+    when the recovery behind another operator's abort, on another stream, has
+    ended too."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("resident run behind a recovery")
+    p = inputs.random_medium((700, 640), seed=73, width=8)
+    # (streams may share a hardware queue, which orders them anyhow: four)
+    streams = [torch.cuda.Stream() for _ in range(5)]
+    ops, Fs, outs, T = [], [], [], 4
+    for s in streams:
+        with torch.cuda.stream(s):
+            ops.append(tdp.operator_from_problem(p))
+            Fs.append(dev(p.F))
+            outs.append(ops[-1].precond(Fs[-1], T, 0.25))
+    torch.cuda.synchronize()
+    want = host(outs[0])
+    ops[0].force_resident_abort(True)
+    with torch.cuda.stream(streams[0]):
+        ops[0].precond(Fs[0], T, 0.25, out=outs[0])
+        over = torch.cuda.Event()
+        over.record()
+    early = []
+    for i in range(1, 5):
+        with torch.cuda.stream(streams[i]):
+            ops[i].precond(Fs[i], T, 0.25, out=outs[i])
+        streams[i].synchronize()
+        early.append(not over.query())
+    torch.cuda.synchronize()
+    assert not any(early), early
+    assert rel(host(outs[0]), want) <= 1e-13
+    for i in range(1, 5):
+        assert np.array_equal(host(outs[i]), want) and ops[i].resident_aborts == 0
