@@ -863,6 +863,9 @@ struct ResGateRecord {
 };
 }  // namespace
 
+// ints at op->res_abort
+static int res_words(const tdp_op *op) { return 4 + res_recover_blocks(op->n[0], op->n[1]); }
+
 // Resident-tile loop (kernel 5): launches of up to TDP_RES_MAXSTEPS steps over
 // every tile of `parts` real fields (2: both parts of Definition 4, in one
 // launch when the tiles fit), ping-ponging between the field pairs (u0, u1)
@@ -929,7 +932,7 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
             a.out_step[1] = last ? n : 0;
             if (!single)
                 TDP_CHECK_HIP(launch_res_init(op->res_slots, res_slot_bytes(f64, k, a.shape) * nt * together,
-                                              op->res_abort, first, f64, s));
+                                              op->res_abort, first ? res_words(op) : 0, f64, s));
             first = false;
             if (f64)
                 TDP_CHECK_HIP(launch_sweep2d_res_f64(a, op->st_step, s));
@@ -957,7 +960,11 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
             r.out[q][0] = variant ? nullptr : Ud + 1;
             r.out[q][1] = Ud + q;
         }
+        // no more compute units than the run's tiles had
+        r.workgroups = std::min(nt * together, op->ncu);
         r.abort_word = op->res_abort;
+        r.ticket = (unsigned long long *)(op->res_abort + 2);
+        r.done = op->res_abort + 4;
         r.host_word = op->res_host + 1;
         TDP_CHECK_HIP(launch_res_recover(r, op->st_step, op->st_step32, f64, s));
     }
@@ -979,7 +986,7 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
     const int shape = res_shape(op, k, parts);
     const int nt = res_tiles(op->n[0], op->n[1], k, f64, shape, nullptr, nullptr);
     if (!op->res_abort &&
-        (hipMalloc(&op->res_abort, sizeof(int)) != hipSuccess ||
+        (hipMalloc(&op->res_abort, sizeof(int) * res_words(op)) != hipSuccess ||
          hipHostMalloc(&op->res_host, 2 * sizeof(int)) != hipSuccess))
         TDP_FAIL(TDP_ENOMEM, "allocation of the abort word failed");
     if (!op->res_id) {

@@ -223,13 +223,15 @@ struct ResArgs {
 };
 hipError_t launch_sweep2d_res_f64(const ResArgs &a, const Stencil<double> &st, hipStream_t s);
 hipError_t launch_sweep2d_res_f32(const ResArgs &a, const Stencil<float> &st, hipStream_t s);
-// every slot word of `bytes` to the empty pattern, the abort word to 0 if clear
-hipError_t launch_res_init(void *slots, size_t bytes, int *abort_word, bool clear, bool f64,
+// every slot word of `bytes` to the empty pattern, `words` ints from the abort word on to 0
+hipError_t launch_res_init(void *slots, size_t bytes, int *abort_word, int words, bool f64,
                            hipStream_t s);
 // The application of a resident run that gave up, redone behind it on the
-// stream (one workgroup; does nothing when the abort word is 0).
+// stream by at most `workgroups` workgroups of a compute unit each (does
+// nothing when the abort word is 0).
 struct ResRecover {
     int ny, nx, parts;
+    int workgroups;
     int64_t nsteps;             // the whole application
     int64_t out_step[2];
     void *u0, *u1;              // field planes
@@ -237,8 +239,11 @@ struct ResRecover {
     const double *tab[2];
     double *out[2][2];
     const int *abort_word;
-    int *host_word;             // pinned: raised when the recovery ran
+    unsigned long long *ticket; // next task; 0 at the start
+    int *done;                  // steps done per block (res_recover_blocks); 0 at the start
+    int *host_word;             // pinned: raised when the recovery runs
 };
+int res_recover_blocks(int ny, int nx);
 hipError_t launch_res_recover(const ResRecover &a, const Stencil<double> &st,
                               const Stencil<float> &st32, bool f64, hipStream_t s);
 int res_tile_rows(bool f64, int shape);
@@ -471,7 +476,7 @@ struct tdp_op {
     int ncu = 0;
     void *res_slots = nullptr;
     size_t res_slots_bytes = 0;
-    int *res_abort = nullptr;
+    int *res_abort = nullptr;              // the abort word, at [2] the recovery's ticket, from [4] its blocks
     uint64_t res_id = 0;                   // this op among the process's resident launches
     int res_aborts = 0;                    // resident launches redone with the blocked sweep
     bool res_off = false;                  // after an abort: the automatic choice leaves kernel 5 out

@@ -1,0 +1,67 @@
+"""What an abort of the resident sweep costs and how it is accounted for (the abort
+is forced from the host; all kernels exit normally)."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2006_16861_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    return torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+def rel(a, b):
+    return float(np.linalg.norm((a - b).ravel()) / max(np.linalg.norm(b.ravel()), 1e-300))
+
+
+def note(msg):
+    print(f"[case] {msg}", file=sys.stderr, flush=True)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,T,variant", [((700, 640), 4, 0), ((700, 640), 4, 1), ((1000, 1050), 3, 0),
+                                           ((65, 40), 30, 1), ((33, 130), 31, 0), ((33, 130), 345, 0)])
+def test_recovery_is_right_and_takes_a_bounded_multiple_of_the_blocked_sweep(n, T, variant, prec):
+    """The recovery is the same recurrence at no more than 20 times the time of
+    the blocked sweep: it holds the stream for milliseconds, not seconds."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    note(f"recovery {n} T={T} variant {variant} prec {prec}")
+    p = inputs.random_medium(n, seed=76, width=6)
+    g = tdp.operator_from_problem(p, prec=prec)
+    F = dev(p.F)
+    out = torch.empty_like(F)
+
+    def ms():
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        torch.cuda.synchronize()
+        e[0].record()
+        g.precond(F, T, 0.25, out=out, variant=variant)
+        e[1].record()
+        torch.cuda.synchronize()
+        return e[0].elapsed_time(e[1])
+
+    g.set_tuning(kernel=2, tb_depth=8, tile=8 if prec else 5)
+    ms()
+    blocked = min(ms() for _ in range(3))
+    want = host(out)
+    g.set_tuning()
+    ms()
+    g.force_resident_abort(True)
+    redone = ms()
+    note(f"  {T * g.nP} steps: blocked {blocked:.3f} ms, aborted and redone {redone:.3f} ms")
+    # FP32: the recovery sums the stencil in another order (the bar of the other
+    # FP32 kernel against kernel comparisons)
+    assert rel(host(out), want) <= (1e-5 if prec else 1e-13)
+    assert redone <= 20 * blocked + 1.0, (blocked, redone)
