@@ -293,9 +293,10 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               32x64 where one of them per compute unit is enough, stays
  *               on chip for up to 4096 steps per launch and swaps k-wide halo
  *               bands with its neighbours through global memory every k steps;
- *               the tiles must all be resident at once, so the resident
- *               launches of a process on one device are ordered one behind the
- *               other, whatever their streams.  Where work of another process
+ *               the tiles must all be resident at once, so of the resident
+ *               launches of a process on one device those that do not fit it
+ *               together are ordered one behind the other, whatever their
+ *               streams.  Where work of another process
  *               holds compute units a wait gives up: with kernel = 5 and in
  *               tdp_gmres_solve the application is redone with the blocked
  *               sweep and the op's tuning goes back to auto; in a

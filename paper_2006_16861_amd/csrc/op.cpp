@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "res_gate.h"
 #include "tdp_internal.h"
 
 namespace tdp {
@@ -107,9 +108,12 @@ using namespace tdp;
 
 extern "C" const char *tdp_last_error(void) { return g_last_error.c_str(); }
 
+static void res_leave(tdp_op *op);
+
 static int free_op(tdp_op *op)
 {
     if (!op) return TDP_OK;
+    res_leave(op);
     if (op->ev) (void)hipEventDestroy(op->ev);
     for (hipEvent_t e : op->tev)
         if (e) (void)hipEventDestroy(e);
@@ -836,32 +840,39 @@ static int issue_steps_abd2(tdp_op *op, const LoopBufs &lb, int T, double rho, i
     return TDP_OK;
 }
 
-// Resident launches of the process on one device run one after the other: two
-// at once, on different streams, could each hold compute units that the
-// other's tiles wait for.  Each waits on the event of the last one.
+// Resident launches of the process on one device, side by side only as far as
+// their tiles fit it together (res_gate.h): two that do not, on different
+// streams, could each hold compute units that the other's tiles wait for.
 namespace {
 struct ResGate {
     std::mutex mu;
-    hipEvent_t ev = nullptr;
-    uint64_t last = 0;             // op of the last launch (0: none yet)
+    ResGateBook book;
 };
 ResGate g_res_gate[64];
 std::atomic<uint64_t> g_res_ids{0};
 
-// Records the gate's event when it goes out of scope: behind the last launch
+// Records the operator's event when it goes out of scope: behind the last launch
 // of the application, its recovery included, and on every error exit too.
 struct ResGateRecord {
-    ResGate *gate = nullptr;
-    uint64_t id = 0;
+    hipEvent_t ev = nullptr;
     hipStream_t s = nullptr;
     ~ResGateRecord()
     {
-        if (!gate) return;
-        if (hipEventRecord(gate->ev, s) == hipSuccess) gate->last = id;
-        else (void)hipStreamSynchronize(s);
+        if (ev && hipEventRecord(ev, s) != hipSuccess) (void)hipStreamSynchronize(s);
     }
 };
 }  // namespace
+
+// The operator's stream has been waited for: no launch needs to wait for its.
+static void res_leave(tdp_op *op)
+{
+    if (op->res_id) {
+        ResGate &gate = g_res_gate[op->device & 63];
+        std::lock_guard<std::mutex> lock(gate.mu);
+        gate.book.forget(op->res_id);
+    }
+    if (op->res_ev) (void)hipEventDestroy(op->res_ev);
+}
 
 // ints at op->res_abort
 static int res_words(const tdp_op *op) { return 4 + res_recover_blocks(op->n[0], op->n[1]); }
@@ -902,10 +913,15 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
     ResGateRecord record;                  // (destroyed before the lock)
     if (!single) {
         lock.lock();
-        if (!gate.ev) TDP_CHECK_HIP(hipEventCreateWithFlags(&gate.ev, hipEventDisableTiming));
-        if (gate.last && gate.last != op->res_id) TDP_CHECK_HIP(hipStreamWaitEvent(s, gate.ev, 0));
-        record.gate = &gate;
-        record.id = op->res_id;
+        void *wait[ResGateBook::kMax];
+        const int n = gate.book.admit(op->res_id, op->res_ev, ResGateBook::units(nt * together),
+                                      std::max(1, op->ncu / 32), wait);
+        for (int i = 0; i < n; ++i) {
+            const hipError_t e = hipStreamWaitEvent(s, (hipEvent_t)wait[i], 0);
+            if (e != hipSuccess) gate.book.withdraw(op->res_id);
+            TDP_CHECK_HIP(e);
+        }
+        record.ev = op->res_ev;
         record.s = s;
     }
     bool first = true;
@@ -989,6 +1005,7 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
         (hipMalloc(&op->res_abort, sizeof(int) * res_words(op)) != hipSuccess ||
          hipHostMalloc(&op->res_host, 2 * sizeof(int)) != hipSuccess))
         TDP_FAIL(TDP_ENOMEM, "allocation of the abort word failed");
+    if (!op->res_ev) TDP_CHECK_HIP(hipEventCreateWithFlags(&op->res_ev, hipEventDisableTiming));
     if (!op->res_id) {
         TDP_CHECK_HIP(hipMemset(op->res_abort, 0, sizeof(int)));
         op->res_host[0] = op->res_host[1] = 0;

@@ -57,7 +57,7 @@
 // 64 columns and the k columns beside the halo columns over all EY rows.
 //
 // Every tile must be resident at once: the host launches no more workgroups
-// than the device holds, and one such launch at a time.  A wait that exceeds
+// than the device holds, over all such launches that may overlap.  A wait that exceeds
 // its poll limit, or sees another tile's abort, raises the abort word and the
 // whole grid leaves early; the host, or k_res_recover behind it on the
 // stream, then redoes the application.

@@ -196,7 +196,7 @@ bool abd_tile_ok(int shape, bool f64);    // tile shapes of the blocked I_abd ke
 // tile in registers for a whole run of steps and swaps k-wide halo bands with
 // the neighbouring tiles through `slots` every k steps.  Every workgroup must
 // be resident at once (workgroups <= compute units x res_workgroups_per_cu,
-// one launch at a time); a wait that does not end sets the abort word and the
+// and launches side by side within res_gate.h); a wait that does not end sets the abort word and the
 // launch ends early with that status.  A grid of one tile and one part waits
 // for nothing and needs no slots.
 #define TDP_RES_MAXSTEPS 4096   // steps of one launch
@@ -478,6 +478,7 @@ struct tdp_op {
     size_t res_slots_bytes = 0;
     int *res_abort = nullptr;              // the abort word, at [2] the recovery's ticket, from [4] its blocks
     uint64_t res_id = 0;                   // this op among the process's resident launches
+    hipEvent_t res_ev = nullptr;           // recorded behind its latest one
     int res_aborts = 0;                    // resident launches redone with the blocked sweep
     bool res_off = false;                  // after an abort: the automatic choice leaves kernel 5 out
     bool res_force_abort = false;          // test hook: every resident wait gives up

@@ -95,3 +95,71 @@ def test_recovery_is_over_before_the_next_resident_run():
     assert rel(host(outs[0]), want) <= 1e-13
     for i in range(1, 5):
         assert np.array_equal(host(outs[i]), want) and ops[i].resident_aborts == 0
+
+
+def test_small_operators_overlap_on_their_streams():
+    """Two operators of 200 x 200 nodes (48 tiles each) on two streams: their
+    resident runs fit the device together and overlap, instead of taking the
+    time of one after the other."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("two small operators on two streams")
+    p = inputs.random_medium((200, 200), seed=72, width=6)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    ops, Fs, outs = [], [], []
+    for s in streams:
+        with torch.cuda.stream(s):
+            ops.append(tdp.operator_from_problem(p))
+            Fs.append(dev(p.F))
+            outs.append(torch.empty_like(Fs[-1]))
+    T = 2000 // ops[0].nP
+
+    def ms(which):
+        torch.cuda.synchronize()
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record(streams[0])
+        streams[1].wait_event(e[0])
+        for _ in range(8):
+            for i in which:
+                with torch.cuda.stream(streams[i]):
+                    ops[i].precond(Fs[i], T, 0.25, out=outs[i])
+        streams[0].wait_stream(streams[1])
+        e[1].record(streams[0])
+        torch.cuda.synchronize()
+        return e[0].elapsed_time(e[1])
+
+    ms([0, 1])
+    one = min(ms([0]) for _ in range(5))
+    both = min(ms([0, 1]) for _ in range(5))
+    note(f"  one {one:.2f} ms, both {both:.2f} ms")
+    assert np.array_equal(host(outs[0]), host(outs[1]))
+    assert all(g.resident_aborts == 0 for g in ops)
+    assert both <= 1.5 * one, (one, both)
+
+
+def test_operators_of_all_sizes_on_their_streams():
+    """Runs of one tile per compute unit or less beside each other and beside
+    ones that need the device for themselves, from five streams in turn: each
+    is bit for bit what the operator gives alone, and none gives up."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("operators of all sizes on five streams")
+    sizes = [(200, 200), (1000, 1050), (300, 260), (512, 512), (65, 64)]
+    ops, Fs, want = [], [], []
+    streams = [torch.cuda.Stream() for _ in sizes]
+    for i, (n, s) in enumerate(zip(sizes, streams)):
+        p = inputs.random_medium(n, seed=78 + i, width=6)
+        with torch.cuda.stream(s):
+            ops.append(tdp.operator_from_problem(p, prec=i % 2))
+            Fs.append(dev(p.F))
+            want.append(ops[-1].precond(Fs[-1], 6, 0.25))
+        s.synchronize()
+    got = []
+    for _ in range(12):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got.append((i, ops[i].precond(Fs[i], 6, 0.25)))
+    torch.cuda.synchronize()
+    for i, U in got:
+        assert torch.equal(U, want[i]), sizes[i]
+    assert all(g.resident_aborts == 0 for g in ops)
