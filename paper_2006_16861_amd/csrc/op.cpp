@@ -905,7 +905,9 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
     a.F = F;
     a.slots = op->res_slots;
     a.abort_word = op->res_abort;
-    a.poll_limit = op->res_force_abort ? 16 : (1 << 21);
+    // a poll takes 0.5 us: 65 ms, long against what a tile waits for a place
+    // beside finite work, and short for one that will not get it
+    a.poll_limit = op->res_force_abort ? 16 : (1 << 17);
     a.wait_bias = op->res_force_abort ? 1 : 0;
     const bool single = nt == 1;           // no exchange, nothing to wait for
     ResGate &gate = g_res_gate[op->device & 63];
