@@ -383,10 +383,24 @@ extern "C" int tdp_op_create(const tdp_op_desc *d, tdp_op **out)
     return TDP_OK;
 }
 
+// Recoveries behind earlier resident runs that have been reached by now: their
+// applications count as aborted, and since other work keeps the tiles from
+// being resident together, the automatic choice takes no more of them.
+static void res_collect(tdp_op *op)
+{
+    if (!op->res_host) return;
+    const int n = *(volatile int *)(op->res_host + 1);
+    if (n == op->res_recovered) return;
+    op->res_aborts += n - op->res_recovered;
+    op->res_recovered = n;
+    op->res_off = true;
+}
+
 extern "C" int tdp_op_query(const tdp_op *op, tdp_op_info *o)
 {
     clear_error();
     if (!op || !o) TDP_FAIL(TDP_EINVAL, "NULL argument");
+    res_collect(const_cast<tdp_op *>(op));
     o->omega_c = op->omega_c;
     o->dt = op->dt;
     o->alpha = op->alpha;
@@ -415,6 +429,7 @@ extern "C" int tdp_op_set_tuning(tdp_op *op, const tdp_tuning *t)
             TDP_FAIL(TDP_EINVAL, "tiles 2, 8, 12 and 13 are FP32 only");
     }
     op->tune = *t;
+    res_collect(op);
     op->res_off = false;
     return TDP_OK;
 }
@@ -874,7 +889,8 @@ static void res_leave(tdp_op *op)
     if (op->res_ev) (void)hipEventDestroy(op->res_ev);
 }
 
-// ints at op->res_abort
+// ints at op->res_abort that every application starts with at 0; behind them the
+// count of the operator's recoveries
 static int res_words(const tdp_op *op) { return 4 + res_recover_blocks(op->n[0], op->n[1]); }
 
 // Resident-tile loop (kernel 5): launches of up to TDP_RES_MAXSTEPS steps over
@@ -983,6 +999,7 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
         r.abort_word = op->res_abort;
         r.ticket = (unsigned long long *)(op->res_abort + 2);
         r.done = op->res_abort + 4;
+        r.count = op->res_abort + res_words(op);
         r.host_word = op->res_host + 1;
         TDP_CHECK_HIP(launch_res_recover(r, op->st_step, op->st_step32, f64, s));
     }
@@ -1004,12 +1021,12 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
     const int shape = res_shape(op, k, parts);
     const int nt = res_tiles(op->n[0], op->n[1], k, f64, shape, nullptr, nullptr);
     if (!op->res_abort &&
-        (hipMalloc(&op->res_abort, sizeof(int) * res_words(op)) != hipSuccess ||
+        (hipMalloc(&op->res_abort, sizeof(int) * (res_words(op) + 1)) != hipSuccess ||
          hipHostMalloc(&op->res_host, 2 * sizeof(int)) != hipSuccess))
         TDP_FAIL(TDP_ENOMEM, "allocation of the abort word failed");
     if (!op->res_ev) TDP_CHECK_HIP(hipEventCreateWithFlags(&op->res_ev, hipEventDisableTiming));
     if (!op->res_id) {
-        TDP_CHECK_HIP(hipMemset(op->res_abort, 0, sizeof(int)));
+        TDP_CHECK_HIP(hipMemset(op->res_abort, 0, sizeof(int) * (res_words(op) + 1)));
         op->res_host[0] = op->res_host[1] = 0;
         op->res_id = ++g_res_ids;
     }
@@ -1271,13 +1288,7 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
     if (Ns > TDP_MAX_STEPS)
         TDP_FAIL(TDP_EINVAL, "N_s = periods_T n_P = %lld exceeds 2^24", (long long)Ns);
     if (variant) TDP_CHECK(ensure_complex_fields(op));
-    // a recovery behind an earlier resident run redid its application: other
-    // work keeps the tiles from being resident together, so no more of them
-    if (op->res_host && *(volatile int *)(op->res_host + 1)) {
-        op->res_host[1] = 0;
-        ++op->res_aborts;
-        op->res_off = true;
-    }
+    res_collect(op);
     // a stream that is being captured by the caller (with use_graph = 0: a
     // capture does not hold another) takes the blocked or streamed sweep, since
     // the resident launches are ordered against each other by events that a

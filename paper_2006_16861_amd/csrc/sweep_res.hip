@@ -673,8 +673,11 @@ __global__ __launch_bounds__(1024) void k_res_recover(ResRecover a, Stencil<T> s
     const T *m = (const T *)a.m, *dn = (const T *)a.dn;
     const double2 *F = (const double2 *)a.F;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        __hip_atomic_store(a.host_word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const int n = *a.count + 1;
+        *a.count = n;
+        __hip_atomic_store(a.host_word, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     // What one wave does for all stands behind branches on scalars: with
     // branches on a lane at the loop's end and start, the compiler sends the
     // other lanes round the loop, through its barriers, while that lane waits

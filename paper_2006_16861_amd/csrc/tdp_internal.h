@@ -241,7 +241,8 @@ struct ResRecover {
     const int *abort_word;
     unsigned long long *ticket; // next task; 0 at the start
     int *done;                  // steps done per block (res_recover_blocks); 0 at the start
-    int *host_word;             // pinned: raised when the recovery runs
+    int *count;                 // recoveries of the operator
+    int *host_word;             // pinned: receives the count as the recovery starts
 };
 int res_recover_blocks(int ny, int nx);
 hipError_t launch_res_recover(const ResRecover &a, const Stencil<double> &st,
@@ -476,12 +477,13 @@ struct tdp_op {
     int ncu = 0;
     void *res_slots = nullptr;
     size_t res_slots_bytes = 0;
-    int *res_abort = nullptr;              // the abort word, at [2] the recovery's ticket, from [4] its blocks
+    int *res_abort = nullptr;              // the abort word, at [2] the recovery's ticket, from [4] its blocks, then its count
     uint64_t res_id = 0;                   // this op among the process's resident launches
     hipEvent_t res_ev = nullptr;           // recorded behind its latest one
     int res_aborts = 0;                    // resident launches redone with the blocked sweep
     bool res_off = false;                  // after an abort: the automatic choice leaves kernel 5 out
     bool res_force_abort = false;          // test hook: every resident wait gives up
-    int *res_host = nullptr;               // pinned: [0] the abort word, [1] raised by a recovery
+    int *res_host = nullptr;               // pinned: [0] the abort word, [1] recoveries started
+    int res_recovered = 0;                 // of these counted in res_aborts
     std::map<std::tuple<int, double, int>, double *> dtables;
 };

@@ -29,6 +29,60 @@ def note(msg):
     print(f"[case] {msg}", file=sys.stderr, flush=True)
 
 
+def test_abort_is_counted_once_its_application_is_over():
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("abort counted by the query")
+    p = inputs.random_medium((150, 140), seed=74, width=4)
+    g = tdp.operator_from_problem(p)
+    g.force_resident_abort(True)
+    g.precond(dev(p.F), 2, 0.25)
+    torch.cuda.synchronize()
+    assert g.resident_aborts == 1
+    assert g.resident_aborts == 1
+
+
+def test_set_tuning_brings_the_resident_sweep_back():
+    """set_tuning after an abort: the next application runs the resident sweep
+    again (and, still forced, aborts again)."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("set_tuning after an abort")
+    p = inputs.random_medium((150, 140), seed=75, width=4)
+    g = tdp.operator_from_problem(p)
+    F = dev(p.F)
+    g.force_resident_abort(True)
+    for i in range(2):
+        g.precond(F, 2, 0.25)
+        torch.cuda.synchronize()
+        g.set_tuning()
+    g.precond(F, 2, 0.25)
+    torch.cuda.synchronize()
+    g.precond(F, 2, 0.25)
+    assert g.resident_aborts == 3
+
+
+def test_every_aborted_application_is_counted():
+    """Several asynchronous applications, all aborted before the host looks."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("three aborts in flight")
+    p = inputs.random_medium((150, 140), seed=75, width=4)
+    g = tdp.operator_from_problem(p)
+    F = dev(p.F)
+    g.precond(F, 2, 0.25)
+    torch.cuda.synchronize()
+    g.force_resident_abort(True)
+    s = torch.cuda.current_stream()
+    busy = torch.zeros(1 << 28, device="cuda")
+    for _ in range(20):
+        busy.add_(1)               # the applications queue up behind this
+    for _ in range(3):
+        g.precond(F, 2, 0.25)
+    s.synchronize()
+    assert g.resident_aborts == 3
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("n,T,variant", [((700, 640), 4, 0), ((700, 640), 4, 1), ((1000, 1050), 3, 0),
                                            ((65, 40), 30, 1), ((33, 130), 31, 0), ((33, 130), 345, 0)])
