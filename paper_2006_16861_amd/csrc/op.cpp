@@ -43,6 +43,8 @@ void clear_error() { g_last_error.clear(); }
 // Captured step loops kept per op (keyed by T, rho, variant and tuning); the
 // cache is emptied when it would grow beyond this.
 static const size_t kMaxGraphs = 16;
+// Device copies of forcing tables (one per T, rho and part), likewise.
+static const size_t kMaxTables = 16;
 
 // Classical fourth-order compact scheme in the cell form (entries by the
 // number of axes on which two corners of a cell differ).
@@ -1042,8 +1044,15 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
             op->res_slots_bytes = n;
         }
     }
-    const int tabvs[2] = {0, 2};
-    for (int q = 0; q < (variant ? 2 : 1); ++q) {
+    const int tabvs[2] = {0, 2}, ntab = variant ? 2 : 1;
+    size_t missing = 0;
+    for (int q = 0; q < ntab; ++q) missing += op->dtables.count(std::make_tuple(T, rho, tabvs[q])) == 0;
+    if (missing && op->dtables.size() + missing > kMaxTables) {
+        TDP_CHECK_HIP(hipStreamSynchronize(op->stream));
+        for (auto &kv : op->dtables) (void)hipFree(kv.second);
+        op->dtables.clear();
+    }
+    for (int q = 0; q < ntab; ++q) {
         const auto key = std::make_tuple(T, rho, tabvs[q]);
         if (op->dtables.count(key)) continue;
         std::vector<double> h = forcing_table(op, T, rho, tabvs[q]);

@@ -1,5 +1,6 @@
 """What an abort of the resident sweep costs and how it is accounted for (the abort
-is forced from the host; all kernels exit normally)."""
+is forced from the host; all kernels exit normally), and what an operator keeps
+for its runs."""
 import sys
 
 import numpy as np
@@ -119,3 +120,34 @@ def test_recovery_is_right_and_takes_a_bounded_multiple_of_the_blocked_sweep(n, 
     # FP32 kernel against kernel comparisons)
     assert rel(host(out), want) <= (1e-5 if prec else 1e-13)
     assert redone <= 20 * blocked + 1.0, (blocked, redone)
+
+
+def test_device_tables_stay_bounded():
+    """A caller that varies rho: the device copies of the forcing tables are
+    bounded, not one more for every value."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    p = inputs.random_medium((60, 50), seed=77, width=4)
+    g = tdp.operator_from_problem(p)
+    F = dev(p.F)
+    out = torch.empty_like(F)
+    T = -(-(1 << 16) // g.nP)
+    note(f"tables of {T * g.nP} steps")
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    rhos = [0.1 + 0.002 * i for i in range(72)]
+    for r in rhos[:24]:
+        g.precond(F, T, r, out=out)
+    before = free()
+    for r in rhos[24:]:
+        g.precond(F, T, r, out=out)
+    grown = before - free()
+    note(f"  {grown / 2**20:.1f} MiB more after {len(rhos) - 24} further tables of 1 MiB")
+    assert grown <= 20 << 20
+    # an earlier value again, after its table has left
+    want = g.precond(F, T, rhos[0]).clone()
+    g.set_tuning(kernel=2, tb_depth=4, tile=5)
+    assert rel(host(g.precond(F, T, rhos[0])), host(want)) <= 1e-11
