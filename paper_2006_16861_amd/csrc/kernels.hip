@@ -557,6 +557,31 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s)
     return hipGetLastError();
 }
 
+// A table from the host to the device in kernel arguments: ordered by the
+// stream, and the host waits for nothing (copies from pageable memory wait for
+// the work before them).  Behind n values, zeros up to n_total.
+constexpr int kTablePart = 448;
+struct TablePart {
+    double v[kTablePart];
+};
+__global__ __launch_bounds__(kTablePart) void k_table_part(double *d, TablePart p, int n)
+{
+    if ((int)threadIdx.x < n) d[threadIdx.x] = p.v[threadIdx.x];
+}
+
+hipError_t launch_table(double *d, const double *h, int64_t n, int64_t n_total, hipStream_t s)
+{
+    for (int64_t i = 0; i < n_total; i += kTablePart) {
+        TablePart p;
+        const int k = (int)std::min<int64_t>(kTablePart, n_total - i);
+        for (int q = 0; q < k; ++q) p.v[q] = i + q < n ? h[i + q] : 0.0;
+        hipLaunchKernelGGL(k_table_part, dim3(1), dim3(kTablePart), 0, s, d + i, p, k);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 __global__ void k_cvt_c128_c64(const double2 *__restrict__ a, float2 *__restrict__ b, int64_t N)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < N;

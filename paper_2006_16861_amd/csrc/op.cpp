@@ -1028,7 +1028,7 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
         TDP_FAIL(TDP_ENOMEM, "allocation of the abort word failed");
     if (!op->res_ev) TDP_CHECK_HIP(hipEventCreateWithFlags(&op->res_ev, hipEventDisableTiming));
     if (!op->res_id) {
-        TDP_CHECK_HIP(hipMemset(op->res_abort, 0, sizeof(int) * (res_words(op) + 1)));
+        TDP_CHECK_HIP(launch_fill_zero(op->res_abort, sizeof(int) * (res_words(op) + 1), op->stream));
         op->res_host[0] = op->res_host[1] = 0;
         op->res_id = ++g_res_ids;
     }
@@ -1055,12 +1055,12 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
     for (int q = 0; q < ntab; ++q) {
         const auto key = std::make_tuple(T, rho, tabvs[q]);
         if (op->dtables.count(key)) continue;
-        std::vector<double> h = forcing_table(op, T, rho, tabvs[q]);
-        h.resize(h.size() + 2 * 64);     // the kernel reads up to 64 steps ahead
+        const std::vector<double> &h = forcing_table(op, T, rho, tabvs[q]);
+        const int64_t n = (int64_t)h.size() + 2 * 64;    // the kernel reads up to 64 steps ahead
         double *d = nullptr;
-        if (hipMalloc(&d, sizeof(double) * h.size()) != hipSuccess)
+        if (hipMalloc(&d, sizeof(double) * n) != hipSuccess)
             TDP_FAIL(TDP_ENOMEM, "device allocation of a forcing table failed");
-        if (hipMemcpy(d, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        if (launch_table(d, h.data(), (int64_t)h.size(), n, op->stream) != hipSuccess) {
             (void)hipFree(d);
             TDP_FAIL(TDP_EHIP, "copy of a forcing table failed");
         }

@@ -309,6 +309,7 @@ hipError_t launch_sweep_abd_f32(const SweepArgs &a, void *uout, const float *rc,
                                 float fa, float fb, hipStream_t s);
 
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
+hipError_t launch_table(double *d, const double *h, int64_t n, int64_t n_total, hipStream_t s);
 hipError_t launch_cvt_c128_to_c64(const void *F, void *Fs, int64_t N, hipStream_t s);
 hipError_t launch_cvt_f64_to_f32(const double *x, float *y, int64_t N, hipStream_t s);
 hipError_t launch_phase_extract(void *U, int64_t N, double c, double s, hipStream_t st);

@@ -151,3 +151,39 @@ def test_device_tables_stay_bounded():
     want = g.precond(F, T, rhos[0]).clone()
     g.set_tuning(kernel=2, tb_depth=4, tile=5)
     assert rel(host(g.precond(F, T, rhos[0])), host(want)) <= 1e-11
+
+
+def test_new_window_does_not_wait_for_other_streams():
+    """An application with a rho that the operator has not seen is as
+    asynchronous as one that it has: the host does not wait for work on the
+    default stream, nor for the operator's own."""
+    import time
+
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("new rho behind queued work")
+    p = inputs.random_medium((150, 140), seed=75, width=4)
+    g = tdp.operator_from_problem(p)
+    F = dev(p.F)
+    out = torch.empty_like(F)
+    busy = torch.zeros(1 << 30, device="cuda")
+
+    def seconds(rho):
+        torch.cuda.synchronize()
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        for _ in range(60):
+            busy.add_(1)
+        e[1].record()
+        t = time.perf_counter()
+        g.precond(F, 2, rho, out=out)
+        t = time.perf_counter() - t
+        torch.cuda.synchronize()
+        return t, 1e-3 * e[0].elapsed_time(e[1])
+
+    seconds(0.25)
+    known, queued = seconds(0.25)
+    fresh, _ = seconds(0.3)
+    note(f"  queued work {queued * 1e3:.1f} ms, host time of a call {known * 1e3:.2f} ms, of one with a new rho {fresh * 1e3:.2f} ms")
+    assert queued >= 0.03
+    assert fresh <= known + 0.3 * queued
