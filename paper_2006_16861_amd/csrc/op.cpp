@@ -1012,6 +1012,15 @@ static int issue_steps_res(tdp_op *op, int T, double rho, int k, const void *F, 
     return TDP_OK;
 }
 
+// bytes of the exchange slots of a run at depth k
+static size_t res_slots_need(const tdp_op *op, int k, int parts)
+{
+    const bool f64 = op->prec == TDP_F64;
+    const int shape = res_shape(op, k, parts);
+    return res_slot_bytes(f64, k, shape) * parts *
+           (size_t)res_tiles(op->n[0], op->n[1], k, f64, shape, nullptr, nullptr);
+}
+
 // Buffers of the resident sweep: exchange slots of every tile, the abort word,
 // its pinned mirror, device copies of the forcing tables the loop reads, and
 // the field pairs that hand over between launches (and hold the fields of the
@@ -1033,12 +1042,20 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
         op->res_id = ++g_res_ids;
     }
     if (nt > 1) {
-        const size_t n = res_slot_bytes(f64, k, shape) * (size_t)nt * parts;
+        size_t n = res_slots_need(op, k, parts);
         if (n > op->res_slots_bytes) {
-            TDP_CHECK_HIP(hipStreamSynchronize(op->stream));
-            (void)hipFree(op->res_slots);
-            op->res_slots = nullptr;
-            op->res_slots_bytes = 0;
+            // at once for both forms, as the automatic choice runs them: to
+            // replace the slots means to wait for the runs that use them
+            for (int v = 0; v < 2 && op->tune.kernel != 5; ++v) {
+                const int kv = res_auto_depth(op, v), pv = v && res_applies(op, kv, 2) ? 2 : 1;
+                if (kv) n = std::max(n, res_slots_need(op, kv, pv));
+            }
+            if (op->res_slots) {
+                TDP_CHECK_HIP(hipStreamSynchronize(op->stream));
+                (void)hipFree(op->res_slots);
+                op->res_slots = nullptr;
+                op->res_slots_bytes = 0;
+            }
             if (hipMalloc(&op->res_slots, n) != hipSuccess)
                 TDP_FAIL(TDP_ENOMEM, "device allocation of the exchange slots failed");
             op->res_slots_bytes = n;

@@ -187,3 +187,33 @@ def test_new_window_does_not_wait_for_other_streams():
     note(f"  queued work {queued * 1e3:.1f} ms, host time of a call {known * 1e3:.2f} ms, of one with a new rho {fresh * 1e3:.2f} ms")
     assert queued >= 0.03
     assert fresh <= known + 0.3 * queued
+
+
+@pytest.mark.parametrize("n", [(60, 50), (150, 140), (700, 640)])
+def test_first_call_does_not_wait_for_other_streams(n):
+    """Nor does a new operator's first application in either form."""
+    import time
+
+    import torch
+    from paper_2006_16861_amd import tdp
+    note(f"first calls of {n} behind queued work")
+    p = inputs.random_medium(n, seed=75, width=4)
+    F = dev(p.F)
+    out = torch.empty_like(F)
+    busy = torch.zeros(1 << 30, device="cuda")
+    tdp.operator_from_problem(p).precond(F, 2, 0.25, out=out)
+    g = tdp.operator_from_problem(p)
+    for variant in (0, 1):
+        torch.cuda.synchronize()
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        for _ in range(60):
+            busy.add_(1)
+        e[1].record()
+        t = time.perf_counter()
+        g.precond(F, 2, 0.25, out=out, variant=variant)
+        t = time.perf_counter() - t
+        torch.cuda.synchronize()
+        queued = 1e-3 * e[0].elapsed_time(e[1])
+        note(f"  variant {variant}: queued work {queued * 1e3:.1f} ms, host time of the call {t * 1e3:.2f} ms")
+        assert queued >= 0.03 and t <= 0.3 * queued
