@@ -110,6 +110,24 @@ using namespace tdp;
 
 extern "C" const char *tdp_last_error(void) { return g_last_error.c_str(); }
 
+// Memory that the operator keeps, made when first needed.  Each buffer is looked
+// at by itself: a failed allocation leaves those made before it, and a later
+// call makes the rest.  (The error is taken back: the next launch would report it.)
+static bool ensure_dev(void **p, size_t bytes)
+{
+    void *q = nullptr;
+    if (!*p && hipMalloc(&q, bytes) != hipSuccess) return (void)hipGetLastError(), false;
+    if (!*p) *p = q;
+    return true;
+}
+static bool ensure_host(void **p, size_t bytes)      // pinned
+{
+    void *q = nullptr;
+    if (!*p && hipHostMalloc(&q, bytes) != hipSuccess) return (void)hipGetLastError(), false;
+    if (!*p) *p = q;
+    return true;
+}
+
 static void res_leave(tdp_op *op);
 
 static int free_op(tdp_op *op)
@@ -554,10 +572,9 @@ int64_t snap_lag(int nP)
 static int ensure_complex_fields(tdp_op *op)
 {
     const size_t fb = 2 * (op->prec == TDP_F64 ? sizeof(double) : sizeof(float)) * op->N;
-    if (!op->u2 && (hipMalloc(&op->u2, fb) != hipSuccess || hipMalloc(&op->u3, fb) != hipSuccess))
+    if (!ensure_dev(&op->u2, fb) || !ensure_dev(&op->u3, fb))
         TDP_FAIL(TDP_ENOMEM, "device allocation of complex recurrence fields failed");
-    if (op->dform == TDP_DAMP_CELL && !op->u4 &&
-        (hipMalloc(&op->u4, fb) != hipSuccess || hipMalloc(&op->u5, fb) != hipSuccess))
+    if (op->dform == TDP_DAMP_CELL && (!ensure_dev(&op->u4, fb) || !ensure_dev(&op->u5, fb)))
         TDP_FAIL(TDP_ENOMEM, "device allocation of complex recurrence fields failed");
     return TDP_OK;
 }
@@ -742,9 +759,8 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
 
 static int ensure_tb_fields(tdp_op *op)
 {
-    if (op->v0) return TDP_OK;
     const size_t fb = (op->prec == TDP_F64 ? sizeof(double) : sizeof(float)) * op->N;
-    if (hipMalloc(&op->v0, fb) != hipSuccess || hipMalloc(&op->v1, fb) != hipSuccess)
+    if (!ensure_dev(&op->v0, fb) || !ensure_dev(&op->v1, fb))
         TDP_FAIL(TDP_ENOMEM, "device allocation of blocked-sweep fields failed");
     return TDP_OK;
 }
@@ -1031,14 +1047,16 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
     const int parts = variant && (int64_t)T * op->nP <= TDP_RES_MAXSTEPS && res_applies(op, k, 2) ? 2 : 1;
     const int shape = res_shape(op, k, parts);
     const int nt = res_tiles(op->n[0], op->n[1], k, f64, shape, nullptr, nullptr);
-    if (!op->res_abort &&
-        (hipMalloc(&op->res_abort, sizeof(int) * (res_words(op) + 1)) != hipSuccess ||
-         hipHostMalloc(&op->res_host, 2 * sizeof(int)) != hipSuccess))
+    if (!ensure_dev((void **)&op->res_abort, sizeof(int) * (res_words(op) + 1)))
         TDP_FAIL(TDP_ENOMEM, "allocation of the abort word failed");
+    if (!op->res_host) {
+        if (!ensure_host((void **)&op->res_host, 2 * sizeof(int)))
+            TDP_FAIL(TDP_ENOMEM, "allocation of the abort word failed");
+        op->res_host[0] = op->res_host[1] = 0;
+    }
     if (!op->res_ev) TDP_CHECK_HIP(hipEventCreateWithFlags(&op->res_ev, hipEventDisableTiming));
     if (!op->res_id) {
         TDP_CHECK_HIP(launch_fill_zero(op->res_abort, sizeof(int) * (res_words(op) + 1), op->stream));
-        op->res_host[0] = op->res_host[1] = 0;
         op->res_id = ++g_res_ids;
     }
     if (nt > 1) {
@@ -1056,7 +1074,7 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
                 op->res_slots = nullptr;
                 op->res_slots_bytes = 0;
             }
-            if (hipMalloc(&op->res_slots, n) != hipSuccess)
+            if (!ensure_dev(&op->res_slots, n))
                 TDP_FAIL(TDP_ENOMEM, "device allocation of the exchange slots failed");
             op->res_slots_bytes = n;
         }
@@ -1075,7 +1093,7 @@ static int ensure_res(tdp_op *op, int T, double rho, int variant, int k)
         const std::vector<double> &h = forcing_table(op, T, rho, tabvs[q]);
         const int64_t n = (int64_t)h.size() + 2 * 64;    // the kernel reads up to 64 steps ahead
         double *d = nullptr;
-        if (hipMalloc(&d, sizeof(double) * n) != hipSuccess)
+        if (!ensure_dev((void **)&d, sizeof(double) * n))
             TDP_FAIL(TDP_ENOMEM, "device allocation of a forcing table failed");
         if (launch_table(d, h.data(), (int64_t)h.size(), n, op->stream) != hipSuccess) {
             (void)hipFree(d);
@@ -1610,24 +1628,23 @@ extern "C" int tdp_op_autotune(tdp_op *op, int periods_T, double rho, int varian
 // GMRES
 static int ensure_krylov(tdp_op *op, int m)
 {
-    if (op->V && op->V_cols >= m + 1) return TDP_OK;
+    if (op->V_cols >= m + 1) return TDP_OK;
     (void)hipStreamSynchronize(op->stream);
+    op->V_cols = 0;                    // until all of it is there
     (void)hipFree(op->V);
     op->V = nullptr;
-    if (hipMalloc(&op->V, (size_t)16 * op->N * (m + 1)) != hipSuccess)
+    if (!ensure_dev(&op->V, (size_t)16 * op->N * (m + 1)))
         TDP_FAIL(TDP_ENOMEM, "Krylov basis allocation (%d x %lld complex) failed", m + 1,
                  (long long)op->N);
-    op->V_cols = m + 1;
-    if (!op->wv) {
-        if (hipMalloc(&op->wv, 16 * op->N) != hipSuccess || hipMalloc(&op->tv, 16 * op->N) != hipSuccess ||
-            hipMalloc(&op->rv, 16 * op->N) != hipSuccess || hipMalloc(&op->xv, 16 * op->N) != hipSuccess)
-            TDP_FAIL(TDP_ENOMEM, "GMRES work vector allocation failed");
-    }
+    for (void **v : {&op->wv, &op->tv, &op->rv, &op->xv})
+        if (!ensure_dev(v, 16 * op->N)) TDP_FAIL(TDP_ENOMEM, "GMRES work vector allocation failed");
     const int nblk = blas_nblocks(op->N);
     const size_t rb = sizeof(double) * 2 * (size_t)nblk * (m + 2);
     if (rb > op->red_bytes) {
         (void)hipFree(op->red);
-        if (hipMalloc(&op->red, rb) != hipSuccess) TDP_FAIL(TDP_ENOMEM, "allocation failed");
+        op->red = nullptr;
+        op->red_bytes = 0;
+        if (!ensure_dev((void **)&op->red, rb)) TDP_FAIL(TDP_ENOMEM, "allocation failed");
         op->red_bytes = rb;
     }
     (void)hipFree(op->dcoef);
@@ -1635,8 +1652,9 @@ static int ensure_krylov(tdp_op *op, int m)
     op->dcoef = nullptr;
     op->hres = nullptr;
     const size_t cb = sizeof(double) * (8 * (size_t)(m + 2));
-    if (hipMalloc(&op->dcoef, cb) != hipSuccess || hipHostMalloc(&op->hres, cb) != hipSuccess)
+    if (!ensure_dev((void **)&op->dcoef, cb) || !ensure_host((void **)&op->hres, cb))
         TDP_FAIL(TDP_ENOMEM, "allocation failed");
+    op->V_cols = m + 1;
     return TDP_OK;
 }
 
@@ -1976,7 +1994,7 @@ extern "C" int tdp_grad_m(const tdp_op *cop, const void *lam, const void *U, dou
     if (!cop || !lam || !U || !grad) TDP_FAIL(TDP_EINVAL, "NULL argument");
     if (misaligned16(lam) || misaligned16(U)) TDP_FAIL(TDP_EINVAL, "complex arrays must be 16-byte aligned");
     tdp_op *op = const_cast<tdp_op *>(cop);
-    if (!op->gcell && hipMalloc(&op->gcell, sizeof(double) * op->Nc) != hipSuccess)
+    if (!ensure_dev((void **)&op->gcell, sizeof(double) * op->Nc))
         TDP_FAIL(TDP_ENOMEM, "allocation failed");
     StreamJoin join(op->user_stream, op->stream, op->ev);
     TDP_CHECK_HIP(launch_grad_cells(op->ndim, op->n, op->omega * op->omega, op->M, lam, U,
