@@ -296,7 +296,8 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               the tiles must all be resident at once, so of the resident
  *               launches of a process on one device those that do not fit it
  *               together are ordered one behind the other, whatever their
- *               streams.  Where work of another process
+ *               streams, and a stream created with a part of the compute
+ *               units takes another kernel.  Where work of another process
  *               holds compute units a wait gives up: with kernel = 5 and in
  *               tdp_gmres_solve the application is redone with the blocked
  *               sweep and the op's tuning goes back to auto; in a

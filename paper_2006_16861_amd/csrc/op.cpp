@@ -233,6 +233,16 @@ static int create_impl(const tdp_op_desc *d, tdp_op *op)
         op->own_stream = true;
         TDP_CHECK_HIP(hipEventCreateWithFlags(&op->ev, hipEventDisableTiming));
     }
+    {   // does the stream have all compute units (its own mask, or a process-wide one)?
+        uint32_t mask[32] = {};
+        const int words = std::min(32, (op->ncu + 31) / 32);
+        if (hipExtStreamGetCUMask(op->stream, words, mask) != hipSuccess) {
+            (void)hipGetLastError();
+        } else {
+            for (int i = 0; i < std::min(op->ncu, 32 * words); ++i)
+                if (!(mask[i / 32] >> (i % 32) & 1)) op->cu_mask = true;
+        }
+    }
     StreamJoin join(op->user_stream, op->stream, op->ev);
     hipStream_t s = op->stream;
 
@@ -588,7 +598,8 @@ static int ensure_complex_fields(tdp_op *op)
 // 128 x 64 tile (FP32) at depth 8; in 3-D the two-step sweep, or
 // (corner entries) the one-step ones by size.
 // Kernel 5 applies to node damping and tables without corner mass terms, on
-// grids whose tiles are resident all at once; elsewhere, and with resident =
+// grids whose tiles are resident all at once (more than one tile: on a stream
+// that has all compute units); elsewhere, and with resident =
 // false (the allocation-free entry point, a stream under capture), the plan
 // falls back to the blocked sweep.
 // The tile shape of a run: the 32-row one where its tiles take a compute unit each.
@@ -604,7 +615,8 @@ static bool res_applies(const tdp_op *op, int k, int parts)
     const bool f64 = op->prec == TDP_F64;
     const int64_t nt = res_tiles(op->n[0], op->n[1], k, f64, res_shape(op, k, parts), nullptr, nullptr);
     if (nt <= 0) return false;
-    return nt == 1 || nt * parts <= (int64_t)op->ncu * res_workgroups_per_cu(k, op->sc, f64);
+    return nt == 1 ||
+           (!op->cu_mask && nt * parts <= (int64_t)op->ncu * res_workgroups_per_cu(k, op->sc, f64));
 }
 
 // The automatic choice's exchange depth, 0 where the resident sweep does not

@@ -476,6 +476,7 @@ struct tdp_op {
     // exchange slots, the abort word and its pinned mirror, device copies of
     // the forcing tables
     int ncu = 0;
+    bool cu_mask = false;                  // the stream has a part of them only
     void *res_slots = nullptr;
     size_t res_slots_bytes = 0;
     int *res_abort = nullptr;              // the abort word, at [2] the recovery's ticket, from [4] its blocks, then its count

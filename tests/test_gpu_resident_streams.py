@@ -163,3 +163,38 @@ def test_operators_of_all_sizes_on_their_streams():
     for i, U in got:
         assert torch.equal(U, want[i]), sizes[i]
     assert all(g.resident_aborts == 0 for g in ops)
+
+
+def test_stream_with_a_part_of_the_compute_units():
+    """A stream created with a mask of compute units holds fewer tiles than the
+    device: the blocked sweep runs on it, bit for bit, not a resident one that
+    gives up and is redone.  A mask of all compute units changes nothing."""
+    import ctypes
+
+    import torch
+    from paper_2006_16861_amd import tdp
+    note("stream with a mask of compute units")
+    p = inputs.random_medium((700, 640), seed=84, width=8)
+    F = dev(p.F)
+    ref = tdp.operator_from_problem(p)
+    resident = ref.precond(F, 4, 0.25)
+    ref.set_tuning(kernel=2, tb_depth=8, tile=5)
+    blocked = ref.precond(F, 4, 0.25)
+    torch.cuda.synchronize()
+    assert not torch.equal(resident, blocked)       # rounding tells them apart
+    hip = ctypes.CDLL("libamdhip64.so")
+    words = 8
+    for cus, want in ((64, blocked), (256, resident)):
+        mask = (ctypes.c_uint32 * words)(*[0xFFFFFFFF if 32 * i < cus else 0 for i in range(words)])
+        h = ctypes.c_void_p()
+        assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(h), words, mask) == 0
+        s = torch.cuda.ExternalStream(h.value)
+        with torch.cuda.stream(s):
+            g = tdp.operator_from_problem(p)
+            got = [g.precond(F, 4, 0.25) for _ in range(2)]
+            s.synchronize()
+            aborts = g.resident_aborts
+            g.close()
+        note(f"  {cus} compute units: distance {rel(host(got[0]), host(want)):.1e}, aborts {aborts}")
+        assert all(torch.equal(U, want) for U in got) and aborts == 0
+        assert hip.hipStreamDestroy(h) == 0
