@@ -708,8 +708,10 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             // at 64^3, 16.7 / 15.8 / 17.9 at 80^3, 42 / 32 / 37 at 131 x 150 x
             // 117, 93 / 65 / 62 at 160^3; FP32 5.9 / 7.6 / 15.5 at 64^3, 12.3 /
             // 12.1 / 17.6 at 100 x 90 x 110, 35 / 31.6 / 35 at 160^3, 112 / 81 / 87
-            // at 256 x 200 x 240
+            // at 256 x 200 x 240.  The second field pair that two steps per launch
+            // need is not worth a refusal: without it, one step
             kern = variant == 0 && op->N < (3 << 17) ? 1 : (!f64 || op->N < (3 << 20) ? 4 : 3);
+            if (kern == 4 && op->no_pair) kern = 3;
             k = kern == 4 ? 2 : 0;
             t = 0;
         }
@@ -1350,8 +1352,9 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
     // the resident launches are ordered against each other by events that a
     // capture cannot hold.  It may not allocate: an earlier call has
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (op->ndim == 2 && !op->own_stream) TDP_CHECK_HIP(hipStreamIsCapturing(op->stream, &cap));
+    if (!op->own_stream) TDP_CHECK_HIP(hipStreamIsCapturing(op->stream, &cap));
     const bool resident = cap == hipStreamCaptureStatusNone;
+    op->no_pair = false;
     int64_t launches;
     {   // allocate before any stream capture: no allocation may happen inside it
         int kern, depth, tile;
@@ -1364,6 +1367,16 @@ static int precond_impl(tdp_op *op, int T, double rho, int variant, const void *
             const bool recover = !pending && op->tune.kernel != 5;
             TDP_CHECK(issue_steps_res(op, T, rho, depth, F, variant, U, recover));
             return recover ? TDP_OK : res_finish(op, T, rho, variant, F, U, direct, pending);
+        }
+        if (kern == 4 && op->tune.kernel == 0 && (op->sc > 3 || op->mc > 2) && !(op->v0 && op->v1) &&
+            (!resident || ensure_tb_fields(op) != TDP_OK)) {
+            clear_error();
+            if (resident) {
+                (void)hipFree(op->v0);
+                op->v0 = nullptr;
+            }
+            op->no_pair = true;
+            sweep_plan(op, variant, &kern, &depth, &tile, resident);
         }
         if (kern == 2 || kern == 4 || kern == 6) TDP_CHECK(ensure_tb_fields(op));
         if (kern == 4) sweep3d_stream2_prepare(op->prec == TDP_F64, tile);
@@ -1484,6 +1497,7 @@ int precond_noalloc_impl(tdp_op *op, int T, double rho, const void *F, void *U,
     }
     LoopBufs lb = bufs;
     lb.table_free = true;
+    op->no_pair = false;
     return issue_steps(op, lb, T, rho, 0, Fin, U);
 }
 

@@ -445,6 +445,7 @@ struct tdp_op {
     void *u0 = nullptr, *u1 = nullptr;      // recurrence fields (prec)
     void *u2 = nullptr, *u3 = nullptr;      // complex fields of the complex-linear variant
     void *v0 = nullptr, *v1 = nullptr;      // second field pair of the blocked sweep
+    bool no_pair = false;                   // this call does without it
     void *Fst = nullptr;                    // staged F (float2) for FP32
     double *scratch = nullptr;              // small device scratch
     size_t scratch_bytes = 0;

@@ -104,6 +104,24 @@ for skip in range(4):
     refused(f"work vector {skip}", 0, 16 * N, skip, op, sol, S)
 refused("krylov coefficients", 0, 8 * 8 * 7, 0, op, sol, S)
 refused("krylov coefficients, pinned", 1, 8 * 8 * 7, 0, op, sol, S)
+
+# 27-point tables in 3-D: one step per launch without the second field pair
+# (the same results, bit for bit), two with it
+p = inputs.random_medium((64, 64, 100), seed=82, width=2)
+F = torch.as_tensor(p.F, device="cuda")
+for prec in (0, 1):
+    g = tdp.operator_from_problem(p, scheme="q1", prec=prec)
+    g.set_tuning(kernel=3, tb_depth=8, tile=0)
+    want = [g.precond(F, 2, 0.25, variant=v) for v in (0, 1)]
+    for skip in (0, 1):
+        print("[case] field pair", skip, "of the 27-point sweep, prec", prec, flush=True)
+        g = tdp.operator_from_problem(p, scheme="q1", prec=prec)
+        for v in (0, 1):
+            shim.shim_fail(0, (4 if prec else 8) * F.numel(), skip, 1)
+            assert torch.equal(g.precond(F, 2, 0.25, variant=v), want[v])
+            assert shim.shim_left() == 0
+        for v in (0, 1):
+            assert torch.equal(g.precond(F, 2, 0.25, variant=v), want[v])
 print("done", flush=True)
 """
 

@@ -97,6 +97,41 @@ def test_recovery_is_over_before_the_next_resident_run():
         assert np.array_equal(host(outs[i]), want) and ops[i].resident_aborts == 0
 
 
+@pytest.mark.parametrize("variant", [0, 1])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_callers_capture_of_a_first_call_27_points(prec, variant):
+    """3-D tables with corner entries: the first call of all may be captured
+    (use_graph = 0), with one step per launch, which needs no second field pair;
+    an eager call after it is the same, bit for bit, with two."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    note(f"capture of a first 27-point call, prec {prec} variant {variant}")
+    p = inputs.random_medium((64, 64, 100), seed=83, width=2)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        g, ref = (tdp.operator_from_problem(p, scheme="q1", prec=prec) for _ in range(2))
+        g.set_tuning(use_graph=0)
+        ref.set_tuning(kernel=3, tb_depth=8, tile=0)
+        F = dev(p.F)
+        out = torch.empty_like(F)
+        if variant:
+            g.set_tuning(kernel=3, tb_depth=8, tile=0)     # makes the complex fields
+            g.precond(F, 1, 0.25, variant=1)
+            g.set_tuning(use_graph=0)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        g.precond(F, 1, 0.25, out=out, variant=variant)
+    for i in range(3):
+        with torch.cuda.stream(s):
+            F.copy_(dev(p.F) * (1 + i))
+            graph.replay()
+            want = ref.precond(F, 1, 0.25, variant=variant)
+            eager = g.precond(F, 1, 0.25, variant=variant)
+        s.synchronize()
+        assert torch.equal(out, want) and torch.equal(eager, want), i
+
+
 def test_small_operators_overlap_on_their_streams():
     """Two operators of 200 x 200 nodes (48 tiles each) on two streams: their
     resident runs fit the device together and overlap, instead of taking the
