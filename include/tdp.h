@@ -271,7 +271,8 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               with node damping and no corner mass entries the resident
  *               tiles (kernel 5) where the grid's tiles fit the device, at the
  *               exchange depth of least cost, on larger
- *               ones (13 * 2^17 nodes up) the streamed 2-D sweep, 8 steps per
+ *               ones (13 * 2^17 nodes up) the streamed 2-D sweep where it takes
+ *               less time, 8 steps per
  *               launch, which has no number here, else the
  *               blocked 2-D sweep on tile 5 (FP64) or 8 (FP32) at depth 8, with
  *               the cell damping on tile 7 (FP64, and FP32 below 3 * 2^16
@@ -343,6 +344,12 @@ typedef struct {
 } tdp_tuning;
 
 int tdp_op_set_tuning(tdp_op *op, const tdp_tuning *t);
+
+/* The kernel that an application of this op takes in this form (variant 0 Table 1,
+ * 1 Definition 4) outside a capture, as its tuning and the library's rules have
+ * it: 1..5 as in tdp_tuning.kernel, 6 the streamed 2-D sweep.  TDP_EINVAL for
+ * other arguments. */
+int tdp_op_planned_kernel(const tdp_op *op, int variant);
 
 /* Test hook of the resident sweep's recovery path (tuning kernel 5): with
  * on = 1, no poll of this op's resident launches succeeds: each gives up

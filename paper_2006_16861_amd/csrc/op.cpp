@@ -648,6 +648,25 @@ static int res_auto_depth(const tdp_op *op, int variant)
     return best;
 }
 
+// The streamed 2-D sweep against the blocked one at depth 8 (32 x 64 tiles in
+// FP64, 128 x 64 in FP32).  A launch of the first takes time by the turns of its
+// loop, the second by its tiles, in FP32 by rounds of two on a compute unit.
+// us per step, streamed and blocked, with turns and tiles: FP64 4.69 and 4.72
+// at 1306^2 (4, 2296), 5.30 and 4.95 at 1340^2 (5, 2352), 5.47 and 5.92 at
+// 1500^2 (5, 3008), 6.27 and 6.63 at 1600^2 (6, 3400), 14.3 and 20.1 at 2999 x
+// 2503 (12, 9964), 4.39 and 6.31 at 27100 x 63 (4, 3388), but 5.28 and 4.76 at 63 x
+// 27100 (5, 2260) and 6.1 and 4.8 at 30 x 60000 (6, 2500): few rows leave the
+// runs few.  FP32 3.72 and 3.77 at 1400^2 (5, 390), 3.74 and 3.95 at 1500^2 (5, 448),
+// 3.71 and 3.58 at 100 x 18000 (5, 375), 4.32 and 4.15 at 1600^2 (6, 510), 4.46 and
+// 5.69 at 1800^2 (6, 646).
+static bool stream_pays(const tdp_op *op)
+{
+    const bool f64 = op->prec == TDP_F64;
+    const int64_t turns = sweep2d_stream_turns(op->n[0], op->n[1], op->ncu);
+    const int64_t tiles = tb2d_tiles(f64 ? 5 : 8, 8, op->n[0], op->n[1]);
+    return f64 ? tiles > 520 * turns : tiles > 2 * op->ncu || tiles > 140 * turns - 320;
+}
+
 static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, int *tile,
                        bool resident = true)
 {
@@ -675,12 +694,8 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             kern = 2;
             k = 8;
             t = f64 ? 5 : 8;
-            // Streamed (internal: kernel 6) where the grid gives its strips
-            // runs that are long against the rows they start with: us per
-            // step, blocked and streamed, FP64 4.4 and 5.2 at 1150^2, 5.6
-            // and 5.5 at 1300^2, 8.0 and 6.3 at 1500 x 1600; FP32 4.6 and 4.35 at
-            // 1500^2
-            if (op->dform == TDP_DAMP_NODE && op->mc <= 2 && op->N >= (13 << 17)) {
+            // Streamed (internal: kernel 6) on large grids where it takes less time
+            if (op->dform == TDP_DAMP_NODE && op->mc <= 2 && op->N >= (13 << 17) && stream_pays(op)) {
                 *kernel = 6;
                 *depth = sweep2d_stream_depth();
                 *tile = t;
@@ -769,6 +784,16 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
     *kernel = kern;
     *depth = k;
     *tile = t;
+}
+
+extern "C" int tdp_op_planned_kernel(const tdp_op *op, int variant)
+{
+    clear_error();
+    if (!op) TDP_FAIL(TDP_EINVAL, "NULL argument");
+    if (variant != 0 && variant != 1) TDP_FAIL(TDP_EINVAL, "variant must be 0 or 1");
+    int kern, depth, tile;
+    sweep_plan(op, variant, &kern, &depth, &tile);
+    return kern;
 }
 
 static int ensure_tb_fields(tdp_op *op)

@@ -33,7 +33,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cmath>
+#include <cstdint>
 
 #include "tdp_internal.h"
 #include "lanes.h"
@@ -336,24 +336,34 @@ void k_sweep2d_stream(const T *__restrict__ u, const T *__restrict__ um, T *__re
     }
 }
 
+// Strips of 64 columns (the last one's lane 63 has no cell beyond it: 63 nodes)
+// and the rows of a run, such that the rounds that the runs take on the
+// resident waves, times a run's turns of the loop, are fewest: runs of K t + 2
+// rows take K (t + 2) iterations, whole turns.  Returns that number.
+int stream_split(int ny, int nx, int ncu, int *strips, int *len)
+{
+    constexpr int K = kSteps, OX = 64 - 2 * K;
+    *strips = nx <= 63 ? 1 : 1 + (nx - 63 + OX - 1) / OX;
+    const int64_t slots = (int64_t)ncu * 4 * kWaves;
+    int64_t best = INT64_MAX;
+    for (int t = 0; t < 4096; ++t) {
+        const int64_t wgs = (int64_t)*strips * ((ny + K * t + 1) / (K * t + 2));
+        const int64_t turns = (wgs + slots - 1) / slots * (t + 2);
+        if (turns < best) {
+            best = turns;
+            *len = K * t + 2;
+        }
+        if (K * t + 2 >= ny) break;
+    }
+    return (int)std::min<int64_t>(best, INT32_MAX);
+}
+
 template <typename T, int SC, int K, int OCC>
 hipError_t launch_stream(const TBArgs &a, const Stencil<T> &st, int ncu, hipStream_t s)
 {
-    constexpr int OX = 64 - 2 * K;
-    const int strips = a.nx <= 63 ? 1 : 1 + (a.nx - 63 + OX - 1) / OX;
-    const int64_t slots = (int64_t)ncu * 4 * OCC;        // resident waves
-    // runs of K t + 2 rows take K (t + 2) iterations, whole turns of the loop
-    int len = 2;
-    double best = INFINITY;
-    for (int t = 0; t < 4096; ++t) {
-        const int64_t wgs = (int64_t)strips * ((a.ny + K * t + 1) / (K * t + 2));
-        const double cost = (double)((wgs + slots - 1) / slots) * (t + 2);
-        if (cost < best) {
-            best = cost;
-            len = K * t + 2;
-        }
-        if (K * t + 2 >= a.ny) break;
-    }
+    static_assert(K == kSteps && OCC == kWaves, "the split is theirs");
+    int strips, len = 2;
+    stream_split(a.ny, a.nx, ncu, &strips, &len);
     const int nrun = (a.ny + len - 1) / len;
     const int per_xcd = (strips * nrun + 7) / 8;
 #define TDP_STREAM(NTS, OUT)                                                                                 \
@@ -376,6 +386,11 @@ hipError_t launch_stream(const TBArgs &a, const Stencil<T> &st, int ncu, hipStre
 }  // namespace
 
 int sweep2d_stream_depth() { return kSteps; }
+int sweep2d_stream_turns(int ny, int nx, int ncu)
+{
+    int strips, len;
+    return stream_split(ny, nx, ncu, &strips, &len);
+}
 hipError_t launch_sweep2d_stream_f64(const TBArgs &a, const Stencil<double> &st, int ncu, hipStream_t s)
 {
     return a.sc > 2 ? launch_stream<double, 3, kSteps, kWaves>(a, st, ncu, s) : launch_stream<double, 2, kSteps, kWaves>(a, st, ncu, s);

@@ -133,6 +133,8 @@ struct TBArgs {
 // The streamed form (sweep2d_stream.hip): exactly sweep2d_stream_depth steps per
 // launch, tables without corner mass entries; `shape` is not used.
 int sweep2d_stream_depth();
+// turns of its loop (eight rows each) that one launch takes on a grid, over all rounds
+int sweep2d_stream_turns(int ny, int nx, int ncu);
 hipError_t launch_sweep2d_stream_f64(const TBArgs &a, const Stencil<double> &st, int ncu, hipStream_t s);
 hipError_t launch_sweep2d_stream_f32(const TBArgs &a, const Stencil<float> &st, int ncu, hipStream_t s);
 

@@ -22,7 +22,7 @@ DAMPING = {"node": 0, "cell": 1}
 SYMBOLS = ("tdp_op_create", "tdp_op_destroy", "tdp_op_query", "tdp_apply_H",
            "tdp_precond_apply", "tdp_precond_apply_complex", "tdp_precond_apply_noalloc",
            "tdp_gmres_solve", "tdp_grad_m", "tdp_op_set_tuning", "tdp_op_autotune",
-           "tdp_op_get_tuning", "tdp_op_force_resident_abort", "tdp_last_error",
+           "tdp_op_get_tuning", "tdp_op_planned_kernel", "tdp_op_force_resident_abort", "tdp_last_error",
            "tdp_batch_create", "tdp_batch_destroy",
            "tdp_batch_set_tuning", "tdp_batch_precond", "tdp_batch_solve", "tdp_batch_autotune")
 
@@ -120,6 +120,7 @@ def load(path: str = LIB_PATH):
     L.tdp_batch_solve.argtypes = [P, ctypes.POINTER(GmresCfg), P, P, P, P]
     L.tdp_batch_autotune.argtypes = [P, P, D, P, I]
     L.tdp_op_force_resident_abort.argtypes = [P, I]
+    L.tdp_op_planned_kernel.argtypes = [P, I]
     L.tdp_last_error.restype = ctypes.c_char_p
     for name in SYMBOLS:
         L[name].restype = L[name].restype if name == "tdp_last_error" else ctypes.c_int
@@ -309,6 +310,11 @@ class Operator:
         _check(load().tdp_op_get_tuning(self._h, ctypes.byref(t)), "tdp_op_get_tuning")
         return {"kernel": t.kernel, "tb_depth": t.tb_depth, "use_graph": t.use_graph,
                 "tile": t.tile}
+
+    def planned_kernel(self, variant=0):
+        """The sweep kernel of an application: 1 to 5 as in set_tuning, 6 the
+        streamed 2-D sweep."""
+        return _check(load().tdp_op_planned_kernel(self._h, int(variant)), "tdp_op_planned_kernel")
 
     @property
     def resident_aborts(self):
