@@ -279,7 +279,8 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               nodes), 4 or (FP32 from 3 * 2^19) 5, from 3 * 2^19 nodes at depth
  *               6; in 3-D the
  *               two-step streamed sweep for tables without corner entries
- *               (FP64 tile 1; FP32 tile 2, tile 0 below 3 * 2^20 nodes) and
+ *               (FP64 tile 1, and kernel 1 on one plane or, below 2^16
+ *               nodes, up to three; FP32 tile 2, tile 0 below 3 * 2^20 nodes) and
  *               for the others kernel 1 below 3 * 2^17 nodes (Table 1 form), then
  *               kernel 4 on tile 0, in FP64 kernel 3 on tile 0 from 3 * 2^20
  *               nodes; tb_depth and

@@ -713,6 +713,15 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             kern = 4;
             k = 2;
             t = f64 ? 1 : (op->N < (3 << 20) ? 0 : 2);
+            // Planes too few to pay for a run's start, in FP64: one step per
+            // launch, one node per thread.  us per step, kernels 4 and 1: 4.7 and
+            // 4.3 at 1 x 200^2, 68 and 49 at 1 x 2000^2, 5.1 and 3.9 at 2 x 1 x
+            // 5000, 9.3 and 8.5 at 2 x 500^2 but 22 and 27 at 2 x 1000^2, 6.0 and
+            // 4.2 at 3 x 64^2, 6.1 and 7.1 at 3 x 300^2
+            if (f64 && (op->n[0] == 1 || (op->n[0] <= 3 && op->N < (1 << 16)))) {
+                kern = 1;
+                k = t = 0;
+            }
         } else {
             // 3-D tables with corner entries (same results, bit for bit, on
             // every kernel).  A small grid gives the streamed kernels too few

@@ -1,8 +1,29 @@
 """Which kernel the untuned choice takes, at sizes where tests of one of them
 depend on it."""
+import sys
+
+import numpy as np
 import pytest
 
+import oracle
+from paper_2006_16861_amd import inputs
+
 pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    return torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+
+
+def host(t):
+    return t.detach().cpu().numpy()
+
+
+def rel(a, b):
+    return float(np.linalg.norm((a - b).ravel()) / max(np.linalg.norm(b.ravel()), 1e-300))
 
 
 def planned(n, prec, variant=0, **kw):
@@ -29,8 +50,24 @@ def test_rules():
         assert planned((1024, 1024), prec, 1, damping="cell") == 2
         # 3-D: two steps per launch; corner entries by size and form
         assert planned((64, 64, 64), prec) == 4 and planned((9, 8, 7), prec, scheme="fd2") == 4
+        for n in ((1, 4, 6), (1, 300, 300), (2, 7, 2), (3, 64, 64)):      # few planes
+            assert planned(n, prec) == (4 if prec else 1), n
+            assert planned(n, prec, 1) == (4 if prec else 1), n
+        assert planned((2, 200, 200), prec) == 4 and planned((4, 4, 4), prec) == 4
         assert planned((64, 64, 95), prec, scheme="q1") == 1
         assert planned((64, 64, 95), prec, 1, scheme="q1") == 4
         assert planned((64, 64, 97), prec, scheme="q1") == 4
         assert planned((148, 146, 147), prec, scheme="q1") == (4 if prec else 3)
         assert planned((9, 8, 7), prec, 1, damping="cell") == 1
+
+
+@pytest.mark.parametrize("n", [(1, 4, 6), (1, 60, 70), (2, 7, 2), (3, 20, 20), (1, 1, 1), (4, 5, 6)])
+def test_few_planes_match_the_oracle(n):
+    """The untuned kernel on 3-D grids of few planes, both forms, at the FP64 bar."""
+    from paper_2006_16861_amd import tdp
+    print(f"[case] few planes {n}", file=sys.stderr, flush=True)
+    p = inputs.random_medium(n, seed=87, width=min(1, min(n) // 2))
+    g, o = tdp.operator_from_problem(p), oracle.Op.from_problem(p)
+    for variant in (0, 1):
+        U = host(g.precond(dev(p.F), 3, 0.25, variant=variant))
+        assert rel(U, o.precond(p.F, 3, 0.25, variant=variant)) <= 1e-10, variant
