@@ -1,5 +1,7 @@
 """Which kernel the untuned choice takes, at sizes where tests of one of them
-depend on it."""
+depend on it, and those tests where they did not reach it: the streamed 2-D
+sweep's strip edges in FP32, and the resident sweep handed over between launches
+in FP32 and under an explicit kernel 5."""
 import sys
 
 import numpy as np
@@ -71,3 +73,60 @@ def test_few_planes_match_the_oracle(n):
     for variant in (0, 1):
         U = host(g.precond(dev(p.F), 3, 0.25, variant=variant))
         assert rel(U, o.precond(p.F, 3, 0.25, variant=variant)) <= 1e-10, variant
+
+
+# the shapes of the streamed sweep's edges, as each precision reaches them
+# (FP32's tiles of 64 x 64 hold more than FP64's of 48 x 64)
+EDGES = [((27100, 63), 0), ((26700, 64), 0), ((15400, 111), 0), ((15301, 112), 0),
+         ((40000, 63), 1), ((40000, 64), 1), ((20500, 111), 1), ((20500, 112), 1),
+         ((2, 860000), 0), ((2, 860000), 1), ((10, 175000), 0), ((19, 92500), 0),
+         ((11, 155000), 1), ((1450, 1400), 0), ((1450, 1400), 1)]
+
+
+@pytest.mark.parametrize("n,prec", EDGES)
+def test_streamed_sweep_runs_at_its_edges(n, prec):
+    """FP64 against the blocked sweep at 1e-13, FP32 equal to it; N_s = 9 to 27."""
+    from paper_2006_16861_amd import tdp
+    print(f"[case] streamed sweep {n} prec {prec}", file=sys.stderr, flush=True)
+    p = inputs.random_medium(n, seed=85, width=min(2, min(n) // 2))
+    g = tdp.operator_from_problem(p, prec=prec)
+    assert g.planned_kernel(0) == 6 and g.planned_kernel(1) == 6
+    F = dev(p.F)
+    for T, variant in ((1, 0), (3, 0), (2, 1)):
+        g.set_tuning(kernel=2, tb_depth=4, tile=5)
+        U = host(g.precond(F, T, 0.25, variant=variant))
+        g.set_tuning()
+        V = host(g.precond(F, T, 0.25, variant=variant))
+        if prec:
+            assert np.array_equal(U, V), (T, variant)
+        else:
+            assert rel(V, U) <= 1e-13, (T, variant)
+
+
+@pytest.mark.parametrize("kernel", [0, 5])
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("nP", [12, 13])
+def test_resident_runs_handed_over(nP, prec, kernel):
+    """More than 4096 steps: two launches, the second of an odd number of steps
+    (n_P = 13: 4121 = 4096 + 25), several tiles.  Against the blocked sweep:
+    FP64 at 1e-11 (it drifts from it by rounding over 4000 steps; the oracle's
+    bar is 1e-10), FP32 equal; FP64 also against the oracle."""
+    from paper_2006_16861_amd import tdp
+    p = inputs.random_medium((60, 130), seed=86, width=5)
+    T = {12: 342, 13: 317}[nP]
+    print(f"[case] {T * nP} steps, prec {prec}, kernel {kernel}", file=sys.stderr, flush=True)
+    g = tdp.Operator(dev(p.c), dev(p.R), p.omega, p.h, prec=prec, steps_per_period=nP)
+    F = dev(p.F)
+    for variant in (0, 1):
+        g.set_tuning(kernel=2, tb_depth=8, tile=8 if prec else 5)
+        U = host(g.precond(F, T, 0.1, variant=variant))
+        g.set_tuning(kernel=kernel, tb_depth=4 if kernel else 0)
+        assert g.planned_kernel(variant) == 5
+        V = host(g.precond(F, T, 0.1, variant=variant))
+        if prec:
+            assert np.array_equal(U, V), variant
+        else:
+            assert rel(V, U) <= 1e-11, variant
+            o = oracle.Op.from_problem(p, nP=nP)
+            assert rel(V, o.precond(p.F, T, 0.1, variant=variant)) <= 1e-10
+    assert g.resident_aborts == 0
