@@ -281,10 +281,11 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               two-step streamed sweep for tables without corner entries
  *               (FP64 tile 1, and kernel 1 on one plane or, below 2^16
  *               nodes, up to three; FP32 tile 2, tile 0 below 3 * 2^20 nodes) and
- *               for the others kernel 1 below 3 * 2^17 nodes (Table 1 form), then
- *               kernel 4 on tile 0, in FP64 kernel 3 on tile 0 from 3 * 2^20
- *               nodes; tb_depth and
- *               tile ignored),
+ *               for the others kernel 1 below 2000 (FP64) or 4000 blocks of
+ *               4 x 64 nodes of a plane (Table 1 form), then kernel 4 on tile 0,
+ *               or kernel 3 on tile 0 where its rounds take less time than
+ *               the planes of kernel 4's, in FP64 from 3 * 2^20 nodes;
+ *               tb_depth and tile ignored),
  *               1 one step per launch, 2 temporally blocked (2-D; with the
  *               cell damping, tiles 5 and 7 in FP64 and 4..7 in FP32, mass
  *               tables without corner entries), 3 streamed along axis 0 (3-D, Table 1

@@ -648,6 +648,40 @@ static int res_auto_depth(const tdp_op *op, int variant)
     return best;
 }
 
+// Default chunk length of the streamed 3-D sweep (kernel 3): halved from 32 (down
+// to 8) until the launch has about 8192 waves, so that small grids still fill the
+// chip (128^3: 8 planes, 2x faster than 32; 256^3: 16).  Returns it; chunks
+// receives the workgroups.
+static int stream_chunk(const tdp_op *op, int tile, int64_t *chunks = nullptr)
+{
+    const int rows = tile == 0 ? 8 : 16;
+    const int waves = tile == 2 ? 8 : 4;
+    const int64_t txy = (int64_t)((op->n[2] + 63) / 64) * ((op->n[1] + rows - 1) / rows);
+    int k = 32;
+    while (k > 8 && txy * ((op->n[0] + k - 1) / k) * waves < 8192) k /= 2;
+    if (chunks) *chunks = txy * ((op->n[0] + k - 1) / k);
+    return k;
+}
+
+// 3-D tables with corner entries: two steps per launch (kernel 4, tile 0, runs of
+// two planes up) against one on the streamed kernel 3.  The first takes time by
+// the planes of a run, over all rounds, the second by rounds of its workgroups.
+// us per step, kernels 4 / 3 with planes and workgroups: FP64 26.2 / 24.2 at
+// 133 x 106 x 85 (13, 476), 24.6 / 24.7 at 89 x 136 x 126 (12, 408), 22.6 / 23.7 at 111 x
+// 107 x 93 (11, 392), 47.7 / 44.3 at 165 x 125 x 135 (24, 1008), 45.1 / 45.5 at 132 x 143 x
+// 179 (22, 918); FP32 26.7 / 25.0 at 165 x 125 x 135 (13, 1008), 24.8 / 24.3 at 233 x 109 x
+// 90 (12, 840), 23.7 / 25.5 at 137 x 182 x 101 (11, 828), 31.6 / 36.2 at 156 x 155 x 136
+// (15, 1200).
+static bool corner_pair_pays(const tdp_op *op)
+{
+    const bool f64 = op->prec == TDP_F64;
+    int64_t chunks;
+    stream_chunk(op, 0, &chunks);
+    const int64_t rounds = (chunks + 4 * op->ncu - 1) / (4 * op->ncu);
+    const int64_t planes = sweep3d_stream2_planes(op->n, 2, f64, op->ncu);
+    return f64 ? 2 * planes < 23 * ((chunks + 2 * op->ncu - 1) / (2 * op->ncu)) : planes < 13 * rounds;
+}
+
 // The streamed 2-D sweep against the blocked one at depth 8 (32 x 64 tiles in
 // FP64, 128 x 64 in FP32).  A launch of the first takes time by the turns of its
 // loop, the second by its tiles, in FP32 by rounds of two on a compute unit.
@@ -724,17 +758,20 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             }
         } else {
             // 3-D tables with corner entries (same results, bit for bit, on
-            // every kernel).  A small grid gives the streamed kernels too few
-            // columns and runs: one step per launch, one node per thread (Def. 4
-            // has only its complex form there and takes the next); then two
-            // steps per launch; in FP64 one again from about 3 * 2^20 nodes.
-            // us per step, kernels 1 / 4 / 3 (27 points): FP64 7.5 / 9.7 / 16.9
-            // at 64^3, 16.7 / 15.8 / 17.9 at 80^3, 42 / 32 / 37 at 131 x 150 x
-            // 117, 93 / 65 / 62 at 160^3; FP32 5.9 / 7.6 / 15.5 at 64^3, 12.3 /
-            // 12.1 / 17.6 at 100 x 90 x 110, 35 / 31.6 / 35 at 160^3, 112 / 81 / 87
-            // at 256 x 200 x 240.  The second field pair that two steps per launch
-            // need is not worth a refusal: without it, one step
-            kern = variant == 0 && op->N < (3 << 17) ? 1 : (!f64 || op->N < (3 << 20) ? 4 : 3);
+            // every kernel): one step per launch, one node per thread, while the
+            // grid is few blocks of 64 x 4 nodes (Def. 4 has only its complex form
+            // there and takes the next), else two steps per launch, or one
+            // streamed where two take longer (corner_pair_pays), in FP64 from
+            // about 3 * 2^20 nodes.  us per step, kernels 1 / 4 / 3 with the blocks
+            // of kernel 1: FP64 5.7 / 9.1 / 16.6 at 38 x 36 x 53 (342), 11.2 /
+            // 11.4 / 16.8 at 85 x 76 x 47 (1615), 12.7 / 11.7 / 16.9 at 69 x 62 x 77
+            // (2208), 57 / 39 / 39 at 376 x 147 x 3 (13912); FP32 10.0 / 10.6 / 15.9
+            // at 189 x 79 x 6 (3780), 11.7 / 10.8 / 16.2 at 302 x 63 x 22 (4832).
+            // The second field pair that two steps per launch need is not worth
+            // a refusal: without it, one step
+            const int64_t blocks = (int64_t)((op->n[2] + 63) / 64) * ((op->n[1] + 3) / 4) * op->n[0];
+            kern = variant == 0 && blocks < (f64 ? 2000 : 4000) ? 1
+                 : (!f64 || op->N < (3 << 20)) && corner_pair_pays(op) ? 4 : 3;
             if (kern == 4 && op->no_pair) kern = 3;
             k = kern == 4 ? 2 : 0;
             t = 0;
@@ -778,14 +815,7 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             // this only bounds how finely a small grid is split
             k = op->sc > 3 || op->mc > 2 ? 8 : 2;
         } else if (k == 0) {
-            // default chunk length: halve from 32 (down to 8) until the launch
-            // has about 8192 waves, so that small grids still fill the chip
-            // (128^3: 8 planes, 2x faster than 32; 256^3: 16)
-            const int rows = t == 0 ? 8 : 16;
-            const int waves = t == 2 ? 8 : 4;
-            const int64_t txy = (int64_t)((op->n[2] + 63) / 64) * ((op->n[1] + rows - 1) / rows);
-            k = 32;
-            while (k > 8 && txy * ((op->n[0] + k - 1) / k) * waves < 8192) k /= 2;
+            k = stream_chunk(op, t);
         }
     } else {
         k = 1;

@@ -621,6 +621,15 @@ static hipError_t launch_stream2_t(const Stream2Args &a, const Stencil<T> &st, h
     return hipGetLastError();
 }
 
+int64_t sweep3d_stream2_planes(const int *n, int zc, bool f64, int ncu)
+{
+    const int64_t ncb = (int64_t)((n[2] + 63) / 64) * ((n[1] + 12) / 13);
+    const int64_t slots =
+        (int64_t)(f64 ? stream2_per_cu<double, 512, 15, false>() : stream2_per_cu<float, 512, 15, false>()) * ncu;
+    const int nrun = stream2_runs(ncb, n[0], zc, slots);
+    return (ncb * nrun + slots - 1) / slots * ((n[0] + nrun - 1) / nrun + 3);
+}
+
 // Tables without corner entries go to the register form.  shape: 0 -> 512 threads on a 66 x 15 level-1 block (64 x 13 outputs, two
 // positions per thread), 1 -> 1024 threads on 66 x 15 (one position per
 // thread), 2 -> 1024 threads on 66 x 31 (64 x 29 outputs; FP32 only, FP64

@@ -291,6 +291,9 @@ hipError_t launch_sweep3d_reg2_f64(const Stream2Args &a, const Stencil<double> &
 hipError_t launch_sweep3d_reg2_f32(const Stream2Args &a, const Stencil<float> &st, int shape,
                                    hipStream_t s);
 void sweep3d_reg2_prepare(bool f64);
+// planes that the workgroups of one launch walk (shape 0, tables with corner
+// entries), the three that a run starts with among them, over all rounds
+int64_t sweep3d_stream2_planes(const int *n, int zc, bool f64, int ncu);
 // runs of at least zc planes per column block that fill whole rounds of `slots`
 int stream2_runs(int64_t ncb, int nz, int zc, int64_t slots);
 

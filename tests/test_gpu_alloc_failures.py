@@ -107,7 +107,7 @@ refused("krylov coefficients, pinned", 1, 8 * 8 * 7, 0, op, sol, S)
 
 # 27-point tables in 3-D: one step per launch without the second field pair
 # (the same results, bit for bit), two with it
-p = inputs.random_medium((64, 64, 100), seed=82, width=2)
+p = inputs.random_medium((100, 100, 100), seed=82, width=2)
 F = torch.as_tensor(p.F, device="cuda")
 for prec in (0, 1):
     g = tdp.operator_from_problem(p, scheme="q1", prec=prec)

@@ -56,10 +56,18 @@ def test_rules():
             assert planned(n, prec) == (4 if prec else 1), n
             assert planned(n, prec, 1) == (4 if prec else 1), n
         assert planned((2, 200, 200), prec) == 4 and planned((4, 4, 4), prec) == 4
-        assert planned((64, 64, 95), prec, scheme="q1") == 1
-        assert planned((64, 64, 95), prec, 1, scheme="q1") == 4
-        assert planned((64, 64, 97), prec, scheme="q1") == 4
+        assert planned((62, 64, 64), prec, scheme="q1") == 1
+        assert planned((62, 64, 64), prec, 1, scheme="q1") == 4
+        assert planned((64, 64, 97), prec, scheme="q1") == (1 if prec else 4)
         assert planned((148, 146, 147), prec, scheme="q1") == (4 if prec else 3)
+        for variant in (0, 1):
+            # narrow rows; where two steps per launch take longer than one; where not
+            assert planned((110, 216, 3), prec, variant, scheme="q1") == 4
+            assert planned((133, 106, 85), prec, variant, scheme="q1") == (4 if prec else 3)
+            assert planned((165, 125, 135), prec, variant, scheme="q1") == 3
+            assert planned((111, 107, 93), prec, variant, scheme="q1") == 4
+            assert planned((131, 150, 117), prec, variant, scheme="q1") == 4
+            assert planned((137, 182, 101), prec, variant, scheme="q1") == 4
         assert planned((9, 8, 7), prec, 1, damping="cell") == 1
 
 

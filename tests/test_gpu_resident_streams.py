@@ -106,7 +106,7 @@ def test_callers_capture_of_a_first_call_27_points(prec, variant):
     import torch
     from paper_2006_16861_amd import tdp
     note(f"capture of a first 27-point call, prec {prec} variant {variant}")
-    p = inputs.random_medium((64, 64, 100), seed=83, width=2)
+    p = inputs.random_medium((100, 100, 100), seed=83, width=2)
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
         g, ref = (tdp.operator_from_problem(p, scheme="q1", prec=prec) for _ in range(2))
