@@ -275,9 +275,9 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               less time, 8 steps per
  *               launch, which has no number here, else the
  *               blocked 2-D sweep on tile 5 (FP64) or 8 (FP32) at depth 8, with
- *               the cell damping on tile 7 (FP64, and FP32 below 3 * 2^16
- *               nodes), 4 or (FP32 from 3 * 2^19) 5, from 3 * 2^19 nodes at depth
- *               6; in 3-D the
+ *               the cell damping on tile 7 (FP64, and FP32 where its tiles
+ *               are at most the compute units), 4 or (FP32 from 3 * 2^19) 5,
+ *               from 3 * 2^19 nodes at depth 6; in 3-D the
  *               two-step streamed sweep for tables without corner entries
  *               (FP64 tile 1, and kernel 1 on one plane or, below 2^16
  *               nodes, up to three; FP32 tile 2, tile 0 below 3 * 2^20 nodes) and

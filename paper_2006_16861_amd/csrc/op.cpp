@@ -776,15 +776,18 @@ static void sweep_plan(const tdp_op *op, int variant, int *kernel, int *depth, i
             k = kern == 4 ? 2 : 0;
             t = 0;
         }
-        // I_abd tiles (same results on each): few rows where workgroups are few,
-        // less depth where HBM is near.  us per step: FP32 tiles 7 / 4 / 5 (at
-        // depth 6) 1.9 / 2.7 / 2.3 at 300^2, 2.9 / 2.7 / 2.9 at 500 x 600, 6.9 / 5.0
-        // / 5.35 at 1024^2, 11.7 / 8.8 / 7.7 at 1500 x 1300, 32 / 23 / 20 at 2400^2;
+        // I_abd tiles (same results on each): few rows where those tiles are at
+        // most the compute units, less depth where HBM is near.  us per step:
+        // FP32 tiles 7 / 4 / 5 (at depth 6) 1.9 / 2.7 / 2.3 at 300^2, 1.88 / 2.63 /
+        // 2.31 at 431 x 419 (243 of tile 7), 2.81 / 2.62 / 2.33 at 251 x 785 (272),
+        // 3.4 / 2.3 at 9000 x 20 (563), 2.9 / 2.7 / 2.9 at 500 x 600, 6.9 / 5.0 / 5.35
+        // at 1024^2, 11.7 / 8.8 / 7.7 at 1500 x 1300, 32 / 23 / 20 at 2400^2;
         // FP64 tile 7 at depths 8 and 6: 5.6 and 6.3 at 800 x 700, 16.9 and 15.3
         // at 1500 x 1300, 48.6 and 46.5 at 2400^2
         if (op->dform == TDP_DAMP_CELL) {
             const bool large = op->N >= (3 << 19);
-            t = f64 || op->N < (3 << 16) ? 7 : (large ? 5 : 4);
+            const bool few = op->ndim == 2 && tb2d_tiles(7, 8, op->n[0], op->n[1]) <= op->ncu;
+            t = f64 || few ? 7 : (large ? 5 : 4);
             if (op->ndim == 2) k = large ? 6 : 8;
         }
     }

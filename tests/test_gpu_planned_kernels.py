@@ -83,6 +83,38 @@ def test_few_planes_match_the_oracle(n):
         assert rel(U, o.precond(p.F, 3, 0.25, variant=variant)) <= 1e-10, variant
 
 
+@pytest.mark.parametrize("n", [(9000, 20), (297, 657), (16 * 256, 48), (16 * 256 + 1, 48)])
+def test_cell_damping_tile_on_long_grids(n):
+    """FP32 with the cell damping: the untuned tile is the one of few rows only
+    where its tiles are at most the compute units (256 and 257 of them).  The
+    same results as on 64 x 64 tiles, bit for bit, in no more time."""
+    import torch
+    from paper_2006_16861_amd import tdp
+    p = inputs.random_medium(n, seed=88, width=4)
+    g = tdp.operator_from_problem(p, prec=1, damping="cell")
+    F = dev(p.F)
+    out = torch.empty_like(F)
+
+    def ms():
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        e[0].record()
+        for _ in range(4):
+            g.precond(F, 10, 0.25, out=out, variant=1)
+        e[1].record()
+        torch.cuda.synchronize()
+        return e[0].elapsed_time(e[1])
+
+    t = {}
+    for name, tun in (("tile 4", dict(kernel=2, tb_depth=8, tile=4)), ("untuned", {})):
+        g.set_tuning(**tun)
+        ms()
+        t[name] = min(ms() for _ in range(5))
+        t[name + " U"] = host(out)
+    print(f"[case]   cell damping {n}: {t['tile 4']:.3f} ms, untuned {t['untuned']:.3f}", file=sys.stderr, flush=True)
+    assert np.array_equal(t["tile 4 U"], t["untuned U"])
+    assert t["untuned"] <= 1.2 * t["tile 4"]
+
+
 # the shapes of the streamed sweep's edges, as each precision reaches them
 # (FP32's tiles of 64 x 64 hold more than FP64's of 48 x 64)
 EDGES = [((27100, 63), 0), ((26700, 64), 0), ((15400, 111), 0), ((15301, 112), 0),
