@@ -308,7 +308,8 @@ int tdp_grad_m(const tdp_op *op, const void *lam, const void *U, double *grad);
  *               asynchronous, it is redone behind the run on the stream; either
  *               way it is counted in tdp_op_info.res_aborts and the op's
  *               automatic choice leaves this kernel out from then on, until
- *               tdp_op_set_tuning.  Where kernel 5 does not apply it falls back
+ *               tdp_op_set_tuning.  A tdp_precond_apply call with kernel = 5 (the
+ *               autotuner's pick where it is the fastest) waits for its run.  Where kernel 5 does not apply it falls back
  *               to the auto choice; a call that the caller captures into a
  *               graph (use_graph = 0, after one eager call of the same form)
  *               takes the blocked or the streamed sweep); inapplicable choices
