@@ -875,7 +875,7 @@ static int issue_steps_tb(tdp_op *op, const LoopBufs &lb, int T, double rho, int
     a.F = Fin;
     for (int64_t j0 = 0; j0 < Ns;) {
         const bool st = streamed && Ns - j0 >= depth;
-        const int k = (int)std::min<int64_t>(streamed && !st ? std::min(depth, 8) : depth, Ns - j0);
+        const int k = (int)std::min<int64_t>(depth, Ns - j0);
         a.u_in = cur;
         a.up_in = prev;
         a.u_out = ncur;

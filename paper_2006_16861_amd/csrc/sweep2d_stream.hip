@@ -36,69 +36,19 @@
 #include <cstdint>
 
 #include "tdp_internal.h"
+#include "buffer.h"
 #include "lanes.h"
 
 namespace tdp {
 
 namespace {
 
-typedef __amdgpu_buffer_rsrc_t Rsrc;
 // steps per launch and waves per SIMD (183 registers in FP64, 170 in FP32, no
 // spills).  At 2999 x 2503 and 2000 x 2000 in FP64 8 steps take 16.7 and 8.4 us
 // each, 10 take 16.3 and 9.6 (fewer own columns a strip), 6 take 20.5 and 9.6; in
 // FP32 8 take 9.5 and 6.0, 10 take 10.3 and 6.7
 constexpr int kSteps = 8, kWaves = 2;
 constexpr unsigned kDropped = 0x7ffffff0u;      // offset of a store outside any buffer
-
-__device__ __forceinline__ Rsrc rsrc_of(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
-}
-__device__ __forceinline__ double f64_of(unsigned lo, unsigned hi)
-{
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-template <int AUX>
-__device__ __forceinline__ void bload(double &v, Rsrc r, unsigned off)
-{
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX);
-    v = f64_of(w.x, w.y);
-}
-template <int AUX>
-__device__ __forceinline__ void bload(float &v, Rsrc r, unsigned off)
-{
-    v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, AUX));
-}
-template <int AUX>
-__device__ __forceinline__ void bload(double2 &v, Rsrc r, unsigned off)
-{
-    typedef unsigned u4 __attribute__((ext_vector_type(4)));
-    const u4 w = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX);
-    v.x = f64_of(w.x, w.y);
-    v.y = f64_of(w.z, w.w);
-}
-template <int AUX>
-__device__ __forceinline__ void bload(float2 &v, Rsrc r, unsigned off)
-{
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX);
-    v.x = __uint_as_float(w.x);
-    v.y = __uint_as_float(w.y);
-}
-template <int AUX>
-__device__ __forceinline__ void bstore(double v, Rsrc r, unsigned off)
-{
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const u2 w = {(unsigned)b, (unsigned)(b >> 32)};
-    __builtin_amdgcn_raw_buffer_store_b64(w, r, off, 0, AUX);
-}
-template <int AUX>
-__device__ __forceinline__ void bstore(float v, Rsrc r, unsigned off)
-{
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, 0, AUX);
-}
 
 // Folded weights of the rows in flight and the update of one node; the two
 // forms of sweep_res.hip.  FP64: weights without the damping factor, which is
@@ -286,7 +236,7 @@ void k_sweep2d_stream(const T *__restrict__ u, const T *__restrict__ um, T *__re
         if (KD > 1) dl[i % KD][lane] = d;
         fetch(p, a + 2);
         T cw = KEEP ? wC[0] : lane_west(C[0]), ce = KEEP ? eC[0] : lane_east(C[0]);
-        T acc = co.part(i, co.before(i, K == 1), C[0], cw, ce, S[0], f, (T)cf.fa[0], (T)cf.fb[0], prev);
+        T acc = co.part(i, co.before(i, false), C[0], cw, ce, S[0], f, (T)cf.fa[0], (T)cf.fb[0], prev);
 #pragma unroll
         for (int l = 1; l <= K; ++l) {
             // level l's row is finished while the next level's is begun: the

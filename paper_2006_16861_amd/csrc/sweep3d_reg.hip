@@ -48,64 +48,16 @@
 #include <cmath>
 
 #include "tdp_internal.h"
+#include "buffer.h"
 #include "lanes.h"
 
 namespace tdp {
 
 namespace {
 
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-
 // offset of a lane or row outside the grid: past every buffer's end, doubled too
 constexpr unsigned kOutside = 0x7ffffff0u;
 constexpr int kAuxNt = 2;            // non-temporal (cache policy bits of buffer accesses)
-
-__device__ __forceinline__ Rsrc rsrc_of(const void *p, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
-}
-
-template <int AUX>
-__device__ __forceinline__ void bload(double &v, Rsrc r, unsigned off)
-{
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX);
-    v = __longlong_as_double((long long)(((unsigned long long)w.y << 32) | w.x));
-}
-template <int AUX>
-__device__ __forceinline__ void bload(float &v, Rsrc r, unsigned off)
-{
-    v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, AUX));
-}
-template <int AUX>
-__device__ __forceinline__ void bload(double2 &v, Rsrc r, unsigned off)
-{
-    typedef unsigned u4 __attribute__((ext_vector_type(4)));
-    const u4 w = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX);
-    v.x = __longlong_as_double((long long)(((unsigned long long)w.y << 32) | w.x));
-    v.y = __longlong_as_double((long long)(((unsigned long long)w.w << 32) | w.z));
-}
-template <int AUX>
-__device__ __forceinline__ void bload(float2 &v, Rsrc r, unsigned off)
-{
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 w = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX);
-    v.x = __uint_as_float(w.x);
-    v.y = __uint_as_float(w.y);
-}
-template <int AUX>
-__device__ __forceinline__ void bstore(double v, Rsrc r, unsigned off)
-{
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const u2 w = {(unsigned)b, (unsigned)(b >> 32)};
-    __builtin_amdgcn_raw_buffer_store_b64(w, r, off, 0, AUX);
-}
-template <int AUX>
-__device__ __forceinline__ void bstore(float v, Rsrc r, unsigned off)
-{
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, 0, AUX);
-}
 
 // the value of the lane to the right; lane 63 gets `last`, which is uniform
 __device__ __forceinline__ float east_or(float v, float last)
