@@ -76,7 +76,7 @@ def test_every_aborted_application_is_counted():
     g.force_resident_abort(True)
     s = torch.cuda.current_stream()
     busy = torch.zeros(1 << 28, device="cuda")
-    for _ in range(20):
+    for _ in range(100):
         busy.add_(1)               # the applications queue up behind this
     for _ in range(3):
         g.precond(F, 2, 0.25)
